@@ -52,5 +52,16 @@ def build(verbose: bool = False) -> str:
     return OUT
 
 
+def build_probe(src: str, out: str) -> str:
+    """A test's own HIP source as a shared library, with the library's flags."""
+    tmp = out + ".tmp"
+    r = subprocess.run([HIPCC, *CFLAGS, "-shared", src, "-o", tmp], capture_output=True, text=True)
+    if r.returncode != 0:
+        sys.stderr.write(r.stdout + r.stderr)
+        raise RuntimeError(f"hipcc failed on {src}")
+    os.replace(tmp, out)
+    return out
+
+
 if __name__ == "__main__":
     build(verbose=True)

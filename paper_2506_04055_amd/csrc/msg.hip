@@ -69,7 +69,9 @@ typedef unsigned v4u __attribute__((ext_vector_type(4)));
 // three bfloat16 parts six (those below 2^-26 dropped): the products of a slot
 // are further slots of the same instruction, so 3 (K + 1) or 6 (K + 1) of them
 // fill its 32 - two instructions for K = 20 split, four for FP32, where one
-// per product takes three or six.  Lane group g holds the KG values
+// per product takes three or six.  (FP32 with K = 8 or 6 takes a third, so that
+// the products of the leading parts have the last to themselves: filter_tile.)
+// Lane group g holds the KG values
 // k = KG g + j; what four groups leave over (k = K) sits in slots they leave
 // free.
 template <int P, int K>
@@ -78,7 +80,7 @@ struct Basis {
     static constexpr bool LEFT = P != 1 && K + 1 > 4 * KG;
     static constexpr int SLOTS = KG + LEFT;                                     // values per lane
     static constexpr int PARTS = P == 0 ? 3 : P;
-    static constexpr int NM = P == 1 ? 1 : ((P == 0 ? 6 : 3) * (K + 1) + 31) / 32;   // instructions
+    static constexpr int NM = P == 1 ? 1 : P == 0 ? (KG == 5 ? 4 : 3) : (3 * (K + 1) + 31) / 32;   // instructions
     static_assert(P == 1 || KG == 5 || KG == 2, "layouts of K = 20, 8 and 6");
 };
 
@@ -112,18 +114,14 @@ __device__ __forceinline__ WSlot weight_slot(int m, int g, int q) {
             part = g == 3 ? -1 : q == 6 ? g : g == 1;
         }
     } else {
-        const int d = 4 * m + q / 2;   // pair of slots
-        k = k0 + (q & 1);
-        part = P == 2 ? d == 0 : d == 0 ? 2 : d == 2 || d == 3 ? 1 : 0;
-        if (P == 2 && d == 3) {
-            k = K;
-            part = g == 0 ? 0 : g == 1 && q == 6 ? 1 : -1;
-        }
-        if (P == 0 && d >= 6) {
-            k = K;
-            part = g > 1 ? -1 : d == 6 ? (g == 0 ? 0 : (q & 1) ? 1 : 2) : g == 0 ? !(q & 1) : -1;
-        }
-        if (!B::LEFT && k == K && (P == 2 ? d == 3 : d >= 6)) part = -1;
+        const int d = 4 * m + q / 2, odd = q & 1;   // pair of slots
+        const bool left = P == 2 ? d == 3 : d > 4 && d != 8;   // the value left over
+        k = left ? K : k0 + odd;
+        if (!left) part = P == 2 ? d == 0 : d == 0 ? 2 : d == 2 || d == 3 ? 1 : 0;
+        else if (!B::LEFT) part = -1;
+        else if (P == 2) part = g == 0 ? 0 : g == 1 && !odd ? 1 : -1;
+        else if (g > 0 || d > 9) part = -1;
+        else part = d == 5 ? (odd ? 0 : 2) : d == 6 ? 1 : odd ? -1 : 0;
     }
     return {k, k <= K ? part : -1};
 }
@@ -269,10 +267,11 @@ struct BOp {
                 put(2, h[1][0], h[1][1], low(h[0][2], h[2][2]), f01);
                 put(3, h[0][0], h[0][1], f01, high(h[0][2], left));
             } else {
-                unsigned l1 = 0, l2 = 0;
-                if constexpr (B::LEFT) l1 = low(h[0][1], h[1][1]), l2 = low(h[0][1], h[2][1]);
+                unsigned l0 = 0, l1 = 0, l2 = 0, l3 = 0;
+                if constexpr (B::LEFT) l0 = h[0][1], l1 = h[1][1], l2 = low(l0, h[2][1]), l3 = low(l1, l0);
                 put(0, h[0][0], h[2][0], h[1][0], h[0][0]);
-                put(1, h[1][0], h[0][0], l1, l2);
+                put(1, h[1][0], l2, l3, l1);
+                put(2, h[0][0], l0, 0, 0);
             }
         }
     }
@@ -335,7 +334,13 @@ __device__ __forceinline__ void stage_pass(const float *__restrict__ A, const fl
 template <int P, int F, int K, int WM, bool SW = false, bool TR = false>
 __device__ __forceinline__ v4f filter_tile(const void *lds, int t, const BOp<P, K> &b, int lane) {
     using WS = WStage<P, F, K, WM, SW>;
-    v4f acc = {0.f, 0.f, 0.f, 0.f};
+    // FP32: what an instruction adds is cut off, not rounded, below the
+    // precision of its largest term, so smaller products summed together with
+    // those of the leading parts pull the filter down (8e-9 of it on average,
+    // which adds up over the atoms of an energy).  The last instruction, which
+    // has the leading parts, sums from zero and is added as a whole (below 1e-10
+    // where it has nothing else, 1e-9 with what K = 20 leaves over for it).
+    v4f acc = {0.f, 0.f, 0.f, 0.f}, hh = acc;
     const int row = 16 * t + (lane & 15), g = lane >> 4;
     // the swizzled piece position depends on the lane only (16 t leaves bits
     // 1-3 of the row alone)
@@ -344,8 +349,10 @@ __device__ __forceinline__ v4f filter_tile(const void *lds, int t, const BOp<P, 
 #pragma unroll
     for (int i = 0; i < Basis<P, K>::NM; i++) {
         const v8bf a = *reinterpret_cast<const v8bf *>(t0 + i * WS::ROWS * WS::LD);
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(TR ? b.m[i] : a, TR ? a : b.m[i], acc, 0, 0, 0);
+        v4f &x = P == 0 && i + 1 == Basis<P, K>::NM ? hh : acc;
+        x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(TR ? b.m[i] : a, TR ? a : b.m[i], x, 0, 0, 0);
     }
+    if constexpr (P == 0) acc += hh;
     return acc;
 }
 

@@ -1,0 +1,75 @@
+// Device functions of the kernels on inputs of a test's own, for what an
+// evaluation's result cannot show: rounding of single products, and kernel
+// variants that only the largest systems take.  Built next to the library
+// (libprobe.so), loaded by tests/test_gpu_device.py.
+#include "../../paper_2506_04055_amd/csrc/msg.hip"
+#include "../../paper_2506_04055_amd/csrc/edge_chain.h"
+
+using namespace mlp;
+
+namespace {
+
+// D[s] = A[s] B[s]^T, A and B 16 x K, one wave per s: a layer's FP32 products
+constexpr int PK = 128;
+__global__ void __launch_bounds__(64) k_products(const float *__restrict__ A, const float *__restrict__ B, float *__restrict__ D) {
+    const int l = threadIdx.x, c = l & 15, g = l >> 4;
+    const float *a = A + ((long)blockIdx.x * 16 + c) * PK, *b = B + ((long)blockIdx.x * 16 + c) * PK;
+    ec_v4f acc = {0.f, 0.f, 0.f, 0.f};
+    for (int k = 0; k < PK; k += 32) {
+        auto op = [&](const float *p) {
+            return ec_op<0>(*reinterpret_cast<const ec_v4f *>(p + k + 8 * g), *reinterpret_cast<const ec_v4f *>(p + k + 8 * g + 4));
+        };
+        const EcOp<0> w = op(a), x = op(b);
+        ec_mul<0, 1>([&](int) { return w.p; }, [&](int) -> const EcOp<0> & { return x; }, [&](int) -> ec_v4f & { return acc; });
+    }
+    for (int r = 0; r < 4; r++) D[(long)blockIdx.x * 256 + (4 * g + r) * 16 + c] = acc[r];
+}
+
+// The radial filter of 16 edges per workgroup: its basis values e~ [edge][32]
+// and the tiles of one pass w [edge][96] (F = 128), of the values or (der) the derivatives.
+template <int K>
+__global__ void __launch_bounds__(256) k_filter(const float *__restrict__ A, const float *__restrict__ c, const float *__restrict__ r, float rc,
+                                                int der, float *__restrict__ e_out, float *__restrict__ w_out) {
+    using B = Basis<0, K>;
+    __shared__ __attribute__((aligned(16))) char lds[WStage<0, 128, K, 32, true>::BYTES];
+    stage_pass<0, 128, K, 32, true>(A, c, 0, lds);
+    if (threadIdx.x >= 64) return;
+    const int lane = threadIdx.x, e = lane & 15, g = lane >> 4;
+    const long edge = 16L * blockIdx.x;
+    const float rr = r[edge + e];
+    float eb[B::SLOTS], db[B::SLOTS];
+    basis_slots<0, K, true>(rr, __builtin_amdgcn_rcpf(rr), 3.14159265358979f / rc, true, g, eb, db);
+    const float *v = der ? db : eb;
+    for (int q = 0; q < B::KG; q++) e_out[(edge + e) * 32 + B::KG * g + q] = v[q];
+    if (B::LEFT && g == 0) e_out[(edge + e) * 32 + K] = v[B::KG];
+    BOp<0, K> b;
+    b.set(v, g);
+    for (int t = 0; t < 6; t++) {
+        const v4f x = filter_tile<0, 128, K, 32, true, true>(lds, t, b, lane);
+        for (int q = 0; q < 4; q++) w_out[(edge + 4 * g + q) * 96 + 16 * t + e] = x[q];
+    }
+}
+
+}  // namespace
+
+namespace mlp {
+int fail(int code, const std::string &) { return code; }
+}  // namespace mlp
+
+extern "C" {
+
+static int done() { return hipGetLastError() == hipSuccess && hipDeviceSynchronize() == hipSuccess ? 0 : -5; }
+
+int probe_products(const float *A, const float *B, float *D, int samples) {
+    k_products<<<samples, 64>>>(A, B, D);
+    return done();
+}
+int probe_filter(int K, const float *A, const float *c, const float *r, float rc, int n16, int der, float *e, float *w) {
+    if (K == 20) k_filter<20><<<n16, 256>>>(A, c, r, rc, der, e, w);
+    else if (K == 8) k_filter<8><<<n16, 256>>>(A, c, r, rc, der, e, w);
+    else if (K == 6) k_filter<6><<<n16, 256>>>(A, c, r, rc, der, e, w);
+    else return -1;
+    return done();
+}
+
+}  // extern "C"

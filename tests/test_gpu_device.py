@@ -1,0 +1,74 @@
+"""Device functions on their own (tests/device/probe.hip, built with the
+library): the rounding of the FP32 operand form, which adds up in the energy of
+a large system but hides in that of a small one."""
+import ctypes
+import os
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+LIB = os.path.join(os.path.dirname(os.path.abspath(__file__)), "device", "libprobe.so")
+U = 2.0 ** -24
+
+
+@pytest.fixture(scope="module")
+def probe():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return ctypes.CDLL(LIB)
+
+
+def dev(a):
+    import torch
+    return torch.as_tensor(np.ascontiguousarray(a)).cuda()
+
+
+def ptr(t):
+    return ctypes.c_void_p(t.data_ptr())
+
+
+def unbiased(label, err, ref, terms):
+    """The mean error of sums of `terms` products is that of rounding to nearest: each of the roundings is below U of the
+    running sum and takes either sign, so the mean over n sums stays within five of its standard deviations U sqrt(terms / n)
+    (relative to the sums' RMS; the running sums are no larger than the results on the average)."""
+    m, s = err.mean() / np.sqrt((ref ** 2).mean()), np.sqrt((err ** 2).mean() / (ref ** 2).mean())
+    tol = 5 * U * np.sqrt(terms / err.size)
+    print(f"[measured] {label}: mean error {m:+.1e} (tol {tol:.1e}), rms {s:.1e}", flush=True)
+    assert abs(m) <= tol
+    assert s <= U * np.sqrt(terms)
+
+
+@pytest.mark.parametrize("kind", ["centred", "positive", "shifted"])
+def test_fp32_products_are_rounded_not_cut(probe, kind):
+    n, K = 2048, 128
+    rng = np.random.default_rng(5)
+    a, b = rng.normal(size=(n, 16, K)) / np.sqrt(K), rng.normal(size=(n, 16, K))
+    if kind == "positive":
+        a, b = abs(a), abs(b)
+    if kind == "shifted":       # the shape of SiLU's outputs
+        b = np.where(b > 0, b, 0.1 * b)
+    A, B, D = dev(a.astype(np.float32)), dev(b.astype(np.float32)), dev(np.zeros((n, 16, 16), np.float32))
+    print(f"[case] products {kind}", flush=True)
+    assert probe.probe_products(ptr(A), ptr(B), ptr(D), n) == 0
+    ref = A.double().cpu().numpy() @ B.double().cpu().numpy().transpose(0, 2, 1)
+    unbiased(f"products {kind}", D.double().cpu().numpy() - ref, ref, K)
+
+
+@pytest.mark.parametrize("K", [20, 8, 6])
+@pytest.mark.parametrize("der", [0, 1])
+def test_fp32_filter_is_rounded_not_cut(probe, K, der):
+    n, rc = 4096, 5.0
+    rng = np.random.default_rng(6)
+    A, c = rng.normal(size=(384, K)).astype(np.float32) / np.float32(np.sqrt(K)), rng.normal(size=384).astype(np.float32)
+    r = rng.uniform(0.9, rc, n).astype(np.float32)
+    dA, dc, dr = dev(A), dev(c), dev(r)
+    e, w = dev(np.zeros((n, 32), np.float32)), dev(np.zeros((n, 96), np.float32))
+    print(f"[case] filter K={K} der={der}", flush=True)
+    assert probe.probe_filter(K, ptr(dA), ptr(dc), ptr(dr), ctypes.c_float(rc), n // 16, der, ptr(e), ptr(w)) == 0
+    rows = (np.arange(96) // 32) * 128 + np.arange(96) % 32
+    W = np.concatenate([c[rows, None], A[rows]], 1).astype(np.float64)
+    ref = e[:, :K + 1].double().cpu().numpy() @ W.T
+    unbiased(f"filter K={K} der={der}", w.double().cpu().numpy() - ref, ref, K + 1)
