@@ -50,6 +50,15 @@ __global__ void __launch_bounds__(256) k_filter(const float *__restrict__ A, con
     }
 }
 
+// sigmoid, SiLU and SiLU' of the edge chains, and the sigmoid's denominator
+__global__ void k_sigmoid(const float *__restrict__ x, int n, float4 *__restrict__ o) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    ec_v4f v = {x[i], 0.f, 0.f, 0.f};
+    const ec_v4f s = ec_silu_d(v);
+    o[i] = make_float4(1.0f + __expf(-x[i]), ec_sigmoid(x[i]), s[0], v[0]);
+}
+
 }  // namespace
 
 namespace mlp {
@@ -69,6 +78,10 @@ int probe_filter(int K, const float *A, const float *c, const float *r, float rc
     else if (K == 8) k_filter<8><<<n16, 256>>>(A, c, r, rc, der, e, w);
     else if (K == 6) k_filter<6><<<n16, 256>>>(A, c, r, rc, der, e, w);
     else return -1;
+    return done();
+}
+int probe_sigmoid(const float *x, int n, float *o) {
+    k_sigmoid<<<(n + 255) / 256, 256>>>(x, n, reinterpret_cast<float4 *>(o));
     return done();
 }
 

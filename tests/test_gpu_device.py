@@ -72,3 +72,19 @@ def test_fp32_filter_is_rounded_not_cut(probe, K, der):
     W = np.concatenate([c[rows, None], A[rows]], 1).astype(np.float64)
     ref = e[:, :K + 1].double().cpu().numpy() @ W.T
     unbiased(f"filter K={K} der={der}", w.double().cpu().numpy() - ref, ref, K + 1)
+
+
+def test_edge_sigmoid_is_divided(probe):
+    x = np.concatenate([np.linspace(-80, 80, 400001), np.random.default_rng(7).normal(size=400000),
+                        [-1000.0, 1000.0, -100.0, 100.0, 0.0, -np.inf, np.inf, np.nan]]).astype(np.float32)
+    X, O = dev(x), dev(np.zeros((x.size, 4), np.float32))
+    print("[case] sigmoid", flush=True)
+    assert probe.probe_sigmoid(ptr(X), x.size, ptr(O)) == 0
+    d, s, silu, dsilu = O.cpu().numpy().T
+    with np.errstate(all="ignore"):
+        want = (np.float32(1) / d).astype(np.float32)
+    print(f"[measured] sigmoid: {(s[:-8] != want[:-8]).mean():.1e} of the quotients differ", flush=True)
+    assert np.array_equal(s, want, equal_nan=True)
+    # the limits, and what an argument that is no number gives
+    assert np.array_equal(silu[-8:-3], [0, 1000, 0, 100, 0]) and np.array_equal(dsilu[-8:-3], [0, 1, 0, 1, 0.5])
+    assert silu[-2] == np.inf and not np.isfinite(silu[-3]) and np.isnan(silu[-1]) and np.isnan(dsilu[-1])
