@@ -546,7 +546,7 @@ struct AlAtomsArgs {
     const int *rowc, *colc, *zsp, *perm;
     const float4 *geom;
     int n, n_local, per_wg, S, p, want_G;
-    float rc, nu, b2, irc, c0, th;   // 1 / rc, sqrt(2 / rc), pi / rc
+    float rc, nu, b2, irc, c0, th, thl;   // 1 / rc, sqrt(2 / rc), pi / rc in two parts
     const char *W;
     const float *vec;
     float *U;
@@ -627,7 +627,7 @@ __global__ void __launch_bounds__(EC_THREADS) __attribute__((amdgpu_waves_per_eu
                 float u, du;
                 envelope(r / A.rc, A.p, u, du);
                 float s1, c1, Y[16];
-                ec_sincos_0pi(A.th * r, s1, c1);
+                ec_sincos_0pi(A.th, A.thl, r, s1, c1);
                 sh16(ed.gm.x * ir, ed.gm.y * ir, ed.gm.z * ir, Y);
 #pragma unroll
                 for (int k = 0; k < 4; k++)
@@ -1304,7 +1304,7 @@ int allegro_evaluate(mlp_model *m, mlp_nbr *g, hipStream_t s, double *energy, fl
         k.p = d.p;
         k.irc = 1.0f / d.rc;
         k.c0 = std::sqrt(2.0f / d.rc);
-        k.th = 3.14159265358979f / d.rc;
+        ec_phase(d.rc, k.th, k.thl);
         k.want_G = forces_user != nullptr;
         k.rc = d.rc;
         k.nu = d.nu;

@@ -531,7 +531,7 @@ struct McEdgeArgs {
     const int *rowc, *colc, *zsp;
     const float4 *geom;
     int nd, per_wg, pe;
-    float rc, irc, c0, th, scale;   // 1 / rc, sqrt(2 / rc), pi / rc, 1 / n_avg
+    float rc, irc, c0, th, thl, scale;   // 1 / rc, sqrt(2 / rc), pi / rc in two parts, 1 / n_avg
     const char *W;                  // the chain's units
     const float *hb;                // first layer: hb0 [S][K]; second: HB [atom][4][K]
     McBlk A;                        // forward: A (written); adjoint: dE/dA
@@ -587,7 +587,7 @@ __device__ __forceinline__ void mc_edge_put(const McEdge &E, const McEdgeArgs &A
         const float r = E.gm.w, ir = 1.0f / r;
         float u, du, s1, c1, Y[16];
         envelope(r / A.rc, A.pe, u, du);
-        ec_sincos_0pi(A.th * r, s1, c1);
+        ec_sincos_0pi(A.th, A.thl, r, s1, c1);
         sh16(E.gm.x * ir, E.gm.y * ir, E.gm.z * ir, Y);
         // rows past the end carry nothing: u = 0 (no MLP has a bias)
 #pragma unroll
@@ -735,7 +735,7 @@ __global__ void __launch_bounds__(EC_THREADS) __attribute__((amdgpu_waves_per_eu
             const float r = gm.w, ir = 1.0f / r;
             float u, du, s1, c1, sk, ck;
             envelope(r / A.rc, A.pe, u, du);
-            ec_sincos_0pi(A.th * r, s1, c1);
+            ec_sincos_0pi(A.th, A.thl, r, s1, c1);
             ec_angle(g, s1, c1, sk, ck);
             // lanes past the atom's edges carry nothing (no MLP has a bias)
             const float bu = e + m < e1 ? A.c0 * ir * u : 0.f;
@@ -1884,7 +1884,7 @@ int mace_evaluate(mlp_model *m, mlp_nbr *g, hipStream_t s, double *energy, float
     ka.rc = a.rc;
     ka.irc = 1.0f / a.rc;
     ka.c0 = std::sqrt(2.0f / a.rc);
-    ka.th = 3.14159265358979f / a.rc;
+    ec_phase(a.rc, ka.th, ka.thl);
     ka.scale = scale;
     ka.MSG = MSG;
     ka.G = g->G.as<float4>();

@@ -59,6 +59,12 @@ __global__ void k_sigmoid(const float *__restrict__ x, int n, float4 *__restrict
     o[i] = make_float4(1.0f + __expf(-x[i]), ec_sigmoid(x[i]), s[0], v[0]);
 }
 
+// sin and cos of pi r / rc as the edge chains take them
+__global__ void k_phase(const float *__restrict__ r, int n, float th, float thl, float2 *__restrict__ o) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) ec_sincos_0pi(th, thl, r[i], o[i].x, o[i].y);
+}
+
 }  // namespace
 
 namespace mlp {
@@ -82,6 +88,12 @@ int probe_filter(int K, const float *A, const float *c, const float *r, float rc
 }
 int probe_sigmoid(const float *x, int n, float *o) {
     k_sigmoid<<<(n + 255) / 256, 256>>>(x, n, reinterpret_cast<float4 *>(o));
+    return done();
+}
+int probe_phase(const float *r, int n, float rc, float *o) {
+    float th, thl;
+    ec_phase(rc, th, thl);
+    k_phase<<<(n + 255) / 256, 256>>>(r, n, th, thl, reinterpret_cast<float2 *>(o));
     return done();
 }
 

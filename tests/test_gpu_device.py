@@ -88,3 +88,18 @@ def test_edge_sigmoid_is_divided(probe):
     # the limits, and what an argument that is no number gives
     assert np.array_equal(silu[-8:-3], [0, 1000, 0, 100, 0]) and np.array_equal(dsilu[-8:-3], [0, 1, 0, 1, 0.5])
     assert silu[-2] == np.inf and not np.isfinite(silu[-3]) and np.isnan(silu[-1]) and np.isnan(dsilu[-1])
+
+
+@pytest.mark.parametrize("rc", [5.0, 4.7, 6.0])
+def test_edge_phase(probe, rc):
+    r = np.linspace(0, rc, 1000001).astype(np.float32)
+    r = r[r <= np.float32(rc)]
+    R, O = dev(r), dev(np.zeros((r.size, 2), np.float32))
+    print(f"[case] phase rc={rc}", flush=True)
+    assert probe.probe_phase(ptr(R), r.size, ctypes.c_float(rc), ptr(O)) == 0
+    th = np.pi * r.astype(np.float64) / np.float64(np.float32(rc))
+    err = O.double().cpu().numpy() - np.stack([np.sin(th), np.cos(th)], 1)
+    print(f"[measured] phase rc={rc}: mean error of sin, cos {err.mean(0)}, max {abs(err).max():.1e}", flush=True)
+    # no offset beyond the series' truncation (2e-9); the series' last sums and the result are rounded once each
+    assert abs(err.mean(0)).max() <= 2.5e-9
+    assert abs(err).max() <= 2 * U
