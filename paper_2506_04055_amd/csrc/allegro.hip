@@ -647,8 +647,9 @@ __global__ void __launch_bounds__(EC_THREADS) __attribute__((amdgpu_waves_per_eu
         };
         // dst[slot][c, m] (+)= nu sum over the slot's rows of tile[row][c] Y_m[row]:
         // per atom and 16-channel tile a product over the atom's rows on the
-        // FP32 matrix instruction (rows past the atom's enter as zeros), of
-        // which the m of the channels' degrees are kept
+        // FP32 matrix instruction (rows past the atom's last enter as that one
+        // times zero: another atom's may not be finite), of which the m of the
+        // channels' degrees are kept
         auto atom_sums = [&](float *dst, int nr, bool add) __attribute__((always_inline)) {
             const int m = lane & 15;
             for (int task = w; task < 4 * na; task += EC_THREADS / 64) {
@@ -659,7 +660,7 @@ __global__ void __launch_bounds__(EC_THREADS) __attribute__((amdgpu_waves_per_eu
                     float x[8], y[8];
 #pragma unroll
                     for (int k = 0; k < 8; k++) {
-                        const int rr = q + 4 * k + g, rc = min(rr, EC_ROWS - 1);
+                        const int rr = q + 4 * k + g, rc = min(rr, q1 - 1);
                         x[k] = tile[rc * AF_TS + 16 * t + m];
                         x[k] = rr < q1 ? x[k] : 0.f;
                         y[k] = ys[rc * 16 + m];
