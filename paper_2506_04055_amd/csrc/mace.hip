@@ -764,9 +764,12 @@ __global__ void __launch_bounds__(EC_THREADS) __attribute__((amdgpu_waves_per_eu
                             for (int c = 0; c < nc; c++) yw[16 * (16 + 3 * (cp_off(p) - 16) + nc * b + c) + m] = Wp[b][c];
                 });
         }
-        // hb of the edges 4 g + r at the channels 16 t + m
+        // hb of the edges 4 g + r at the channels 16 t + m (zero for a wave
+        // without a tile: any other atom's may not be finite)
         v4f h[NC][2];
-        {
+#pragma unroll
+        for (int c = 0; c < NC; c++) h[c][0] = h[c][1] = z4;
+        if (i < na) {
             const int jr = LAY == 0 ? A.zsp[j] : j;
 #pragma unroll
             for (int r = 0; r < 4; r++) {

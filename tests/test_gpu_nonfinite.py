@@ -49,6 +49,7 @@ MODELS = {
     # weights, atoms, and how many cutoffs an energy and a force reach
     "allegro": (lambda: synth.make_allegro_weights(2, seed=1, bias_scale=0.1), 1500, 0, 1),
     "mace": (lambda: synth.make_mace_weights(2, seed=1, bias_scale=0.1), 1500, 2, 4),
+    "mace_two_waves": (lambda: synth.make_mace_weights(2, seed=1, bias_scale=0.1), 900, 2, 4),
     "painn32": (lambda: synth.make_weights(32, 8, 2, 2, seed=1, bias_scale=0.1), 1500, 2, 4),
     "painn64": (lambda: synth.make_weights(64, 20, 2, 2, seed=1, bias_scale=0.1), 1500, 2, 4),
 }
