@@ -33,15 +33,15 @@ static inline int nblk(long n, int t) { return (int)((n + t - 1) / t); }
 // The layers' node work runs in node.hip, the factorised first layer's
 // products in gemm.hip.
 // ---------------------------------------------------------------------------
-static void gemm(hipStream_t s, int prec, const float *A, int lda, const PackedW &B, float *C, int ldc, int M) {
-    if (M <= 0) return;
+static int gemm(hipStream_t s, int prec, const float *A, int lda, const PackedW &B, float *C, int ldc, int M) {
+    if (M <= 0) return 0;
     ProfScope ps(PK_GEMM, s);
-    node_gemm(s, prec, GE_STORE, A, lda, B, C, ldc, M);
+    return node_gemm(s, prec, GE_STORE, A, lda, B, C, ldc, M);
 }
 // Two independent products, the second over three times the rows (s and v of
 // the first layer), in one launch where they fit (on 192 atoms a launch is the
 // product's time).
-static void gemm_sv(hipStream_t s, int prec, const float *A0, int lda0, const PackedW &B0, float *C0, int ldc0,
+static int gemm_sv(hipStream_t s, int prec, const float *A0, int lda0, const PackedW &B0, float *C0, int ldc0,
                     const float *A1, int lda1, const PackedW &B1, float *C1, int ldc1, int M) {
     GemmBatch b;
     b.n = 2;
@@ -49,10 +49,11 @@ static void gemm_sv(hipStream_t s, int prec, const float *A0, int lda0, const Pa
     b.A[1] = A1, b.lda[1] = lda1, b.B[1] = B1, b.C[1] = C1, b.ldc[1] = ldc1, b.M[1] = 3 * M;
     {
         ProfScope ps(PK_GEMM, s);
-        if (node_gemm_batch(s, prec, b) != -1) return;
+        const int rc = node_gemm_batch(s, prec, b);
+        if (rc != -1) return rc;
     }
-    gemm(s, prec, A0, lda0, B0, C0, ldc0, M);
-    gemm(s, prec, A1, lda1, B1, C1, ldc1, 3 * M);
+    if (int rc = gemm(s, prec, A0, lda0, B0, C0, ldc0, M)) return rc;
+    return gemm(s, prec, A1, lda1, B1, C1, ldc1, 3 * M);
 }
 
 // ---------------------------------------------------------------------------
@@ -69,7 +70,6 @@ static void fill_zero(hipStream_t s, float *p, long count) {
     if (count > 0) k_fill_zero<<<nblk(count, 256), 256, 0, s>>>(p, count);
 }
 
-// Readout: U_i, and the gradient seed dE/dh5 = w6 o silu'(h5) on local atoms.
 // Sum over the 16 lanes of a DPP row.
 __device__ __forceinline__ float row16_sum(float x) {
     x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x128, 0xF, 0xF, false));   // row_ror:8
@@ -270,9 +270,9 @@ int first_layer_table(mlp_model *m, hipStream_t s, float *tmp) {
     const int P = node_operands(m->precision);
     const LayerW L = m->layer(0);
     // the same GEMMs as the later layers' node MLPs, on the S embedding rows
-    node_gemm(s, P, GE_BIAS_SILU, m->at(m->off_emb), F, m->pk_phi0[0], tmp, F, S, L.b1, tmp + (long)S * F, F);
-    node_gemm(s, P, GE_BIAS, tmp + (long)S * F, F, m->pk_phi0[1], m->phi0_dev, 3 * F, S, L.b2);
-    return hipGetLastError() == hipSuccess ? 0 : -5;
+    if (int rc = node_gemm(s, P, GE_BIAS_SILU, m->at(m->off_emb), F, m->pk_phi0[0], tmp, F, S, L.b1, tmp + (long)S * F, F))
+        return rc;
+    return node_gemm(s, P, GE_BIAS, tmp + (long)S * F, F, m->pk_phi0[1], m->phi0_dev, 3 * F, S, L.b2);
 }
 
 // Species-scaled first-layer filter weights (CS = S SB columns of basis
@@ -468,7 +468,8 @@ int evaluate(mlp_model *m, mlp_nbr *g, hipStream_t s, double *energy, float *for
             la.ldp = l0.ldp;
             la.ldr = l0.ldr;
             if ((rc = msg_l0_basis_sums(s, K, m->S, la))) return fail(rc, "first-layer kernel launch failed");
-            gemm_sv(s, P, la.P, l0.ldp, m->pk_l0[0], A.sn[0], 2 * F, la.R, l0.ldr, m->pk_l0[1], A.v1[0], F, ndst);
+            if ((rc = gemm_sv(s, P, la.P, l0.ldp, m->pk_l0[0], A.sn[0], 2 * F, la.R, l0.ldr, m->pk_l0[1], A.v1[0], F, ndst)))
+                return fail(rc, "first-layer product launch failed");
         } else {
             MsgArgs ma = msg_args(g, m, L, hop_dst);
             ma.layer0 = t == 0;
@@ -526,7 +527,8 @@ int evaluate(mlp_model *m, mlp_nbr *g, hipStream_t s, double *energy, float *for
             // covers the rows through nfar (zero past ndst, as gs1 and gv1).
             L0Args la = l0_args(g, m, hop_src);
             float *Qs = A.work, *Qv = A.work + (long)n * l0.ldq;
-            gemm_sv(s, P, A.gs1, F, m->pk_l0[2], Qs, l0.ldq, A.gv1, F, m->pk_l0[3], Qv, l0.ldq, nfar);
+            if ((rc = gemm_sv(s, P, A.gs1, F, m->pk_l0[2], Qs, l0.ldq, A.gv1, F, m->pk_l0[3], Qv, l0.ldq, nfar)))
+                return fail(rc, "first-layer product launch failed");
             la.Qs = Qs;
             la.Qv = Qv;
             la.ldq = l0.ldq;
