@@ -1316,9 +1316,12 @@ int allegro_evaluate(mlp_model *m, mlp_nbr *g, hipStream_t s, double *energy, fl
         k.G = g->G.as<float4>();
         k.per_wg = ec_per_wg(n, E, d.rc, g->skin);
         const int nb = nblk(n, k.per_wg);
-        if (P == 0) k_al_atoms<0><<<nb, EC_THREADS, 0, s>>>(k);
-        else if (P == 1) k_al_atoms<1><<<nb, EC_THREADS, 0, s>>>(k);
-        else k_al_atoms<2><<<nb, EC_THREADS, 0, s>>>(k);
+        {
+            ProfScope ps(PK_GEMM, s);
+            if (P == 0) k_al_atoms<0><<<nb, EC_THREADS, 0, s>>>(k);
+            else if (P == 1) k_al_atoms<1><<<nb, EC_THREADS, 0, s>>>(k);
+            else k_al_atoms<2><<<nb, EC_THREADS, 0, s>>>(k);
+        }
         HIP_TRY(hipGetLastError());
         if ((rc = launch_energy(s, k.U, k.perm, n, g->n_local, energy, atom_energy_user, n_seg, seg_dev,
                                 reinterpret_cast<double *>(base + (n + 64 + 63) / 64 * 64))))

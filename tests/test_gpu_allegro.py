@@ -161,6 +161,26 @@ def test_al_one_kernel_edges(mlp, make, precision):
     assert float(r["sys"].energy.item()) == r["E"]
 
 
+@pytest.mark.parametrize("make", [_narrow, _other])
+def test_al_profile_counts_the_layers(mlp, make):
+    # the layers' time is reported as node_gemm on the one-kernel path, as on the other
+    import torch
+    s, kw = make()
+    h, w = synth.make_allegro_weights(2, seed=12, **kw)
+    d = mlp.System(mlp.Model(h, w, "bf16"), s.pos, s.species, s.box, skin=0.5)
+    d.compute()
+    mlp.mlp_profile_reset()
+    mlp.mlp_profile_enable(True)
+    try:
+        d.compute()
+        torch.cuda.synchronize()
+        ms, launches = mlp.mlp_profile_read("node_gemm")
+    finally:
+        mlp.mlp_profile_enable(False)
+        mlp.mlp_profile_reset()
+    assert launches > 0 and ms > 0.0
+
+
 def test_al_header_errors(mlp):
     h, w = synth.make_allegro_weights(1, seed=0)
     with pytest.raises(mlp.MLPError):
