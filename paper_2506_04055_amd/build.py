@@ -14,6 +14,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libmlp.so")
 BUILD = os.path.join(HERE, "_build")
+PROBE = os.path.join(os.path.dirname(HERE), "tests", "device", "libprobe.so")
 SOURCES = ["api.hip", "nbr.hip", "painn.hip", "prof.hip", "node_p2.hip", "node_p0.hip", "node_p1.hip", "gemm.hip", "node.hip", "msg.hip", "server.hip", "md.hip", "noalloc.hip", "allegro.hip",
            "mace.hip"]
 ARCH = os.environ.get("MLP_OFFLOAD_ARCH", "gfx950")
@@ -52,15 +53,21 @@ def build(verbose: bool = False) -> str:
     return OUT
 
 
-def build_probe(src: str, out: str) -> str:
-    """A test's own HIP source as a shared library, with the library's flags."""
-    tmp = out + ".tmp"
-    r = subprocess.run([HIPCC, *CFLAGS, "-shared", src, "-o", tmp], capture_output=True, text=True)
+def build_probe() -> str:
+    """The tests' device probe (tests/device/probe.hip) as a library of its own, with the same flags."""
+    tmp = PROBE + ".tmp"
+    r = subprocess.run([HIPCC, *CFLAGS, "-shared", os.path.join(os.path.dirname(PROBE), "probe.hip"), "-o", tmp],
+                       capture_output=True, text=True)
     if r.returncode != 0:
         sys.stderr.write(r.stdout + r.stderr)
-        raise RuntimeError(f"hipcc failed on {src}")
-    os.replace(tmp, out)
-    return out
+        raise RuntimeError("hipcc failed on probe.hip")
+    os.replace(tmp, PROBE)
+    return PROBE
+
+
+def probe_lib() -> str:
+    """The built probe; built first where there is none."""
+    return PROBE if os.path.exists(PROBE) else build_probe()
 
 
 if __name__ == "__main__":

@@ -537,7 +537,10 @@ __global__ void k_al_geom_bwd(const int *__restrict__ rowc, int n, const float4 
 // atoms of water in FP32: 0.84 ms and 0.12 ms (0.20 with one atom to a
 // workgroup and SiLU' formed again in the adjoint).
 // ---------------------------------------------------------------------------
-constexpr int AF_TS = 68, AF_ENV = 224;
+// (atoms of a run: what LDS holds of env.  With six, a gas of one neighbour per
+// atom filled six rows of 128: 100,000 atoms, split bf16, 1.39 ms, 0.43 so, and
+// 0.53 with a kernel per step; of eight neighbours 1.64, 1.04 and 3.39 ms)
+constexpr int AF_TS = 68, AF_ENV = 224, AF_SLOTS = 60;
 // constants in LDS: biases and the output vector, zero-padded
 constexpr int AF_B1 = 0, AF_B2 = 16, AF_B3 = 32, AF_B4 = 64, AF_L1 = 128, AF_L2 = 192, AF_O1 = 256, AF_W2 = 288,
               AF_VEC = 320;
@@ -559,12 +562,12 @@ __global__ void __launch_bounds__(EC_THREADS) __attribute__((amdgpu_waves_per_eu
     constexpr int N1 = 24 / EcStream<P>::U, N2 = 56 / EcStream<P>::U, N3 = 32 / EcStream<P>::U;   // stages
     __shared__ __attribute__((aligned(16))) char wst[2 * EcStream<P>::SB];
     __shared__ __attribute__((aligned(16))) float tile[EC_ROWS * AF_TS], ys[EC_ROWS * 16], eg[EC_ROWS * 8],
-        en[EC_SLOTS * AF_ENV], cb[AF_VEC], es[EC_ROWS];
-    __shared__ int roff[EC_SLOTS + 1];
+        en[AF_SLOTS * AF_ENV], cb[AF_VEC], es[EC_ROWS];
+    __shared__ int roff[AF_SLOTS + 1];
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4,
               row = 16 * w + (lane & 15);
     const v4f z4 = v4f{0.f, 0.f, 0.f, 0.f};
-    for (int q = tid; q < EC_SLOTS * AF_ENV; q += EC_THREADS) en[q] = 0.f;   // the padding stays zero
+    for (int q = tid; q < min(AF_SLOTS, A.per_wg + 1) * AF_ENV; q += EC_THREADS) en[q] = 0.f;   // the padding stays zero
     if (tid < AF_VEC) cb[tid] = A.vec[tid];
     const char *W1 = A.W, *W2 = W1 + N1 * EcStream<P>::SB, *W3 = W2 + N2 * EcStream<P>::SB;
     EcStream<P> st;
@@ -594,15 +597,15 @@ __global__ void __launch_bounds__(EC_THREADS) __attribute__((amdgpu_waves_per_eu
             E.pm = A.perm[a_ + E.slot];
         }
     };
-    int base = A.rowc[a], off = ec_row_off(A.rowc, lane, a, a1) - base;
+    int base = A.rowc[a], off = ec_row_off<AF_SLOTS>(A.rowc, lane, a, a1) - base;
     Edge ed;
     bool have = false;   // the run's first piece is in ed
     while (a < a1) {
         __syncthreads();   // the last reads of the previous run's LDS
-        const EcRun run = ec_run(lane, a, a1, off);
+        const EcRun run = ec_run<AF_SLOTS>(lane, a, a1, off);
         const int na = run.na, nch = run.nch, total = run.total;
         // the row offsets of the run after this one
-        const int an = min(a + na, a1), nbase = A.rowc[an], noff = ec_row_off(A.rowc, lane, an, a1);
+        const int an = min(a + na, a1), nbase = A.rowc[an], noff = ec_row_off<AF_SLOTS>(A.rowc, lane, an, a1);
         if (total == 0) {
             if (tid < na) A.U[a + tid] = 0.f;
             a += na;
@@ -895,7 +898,7 @@ __global__ void __launch_bounds__(EC_THREADS) __attribute__((amdgpu_waves_per_eu
                 if (pass == 2) {   // ---- phase 3
                     if (nch == 1 && an < a1) {   // the next run's first edges, behind this phase
                         const int o = noff - nbase;
-                        const EcRun nx = ec_run(lane, an, a1, o);
+                        const EcRun nx = ec_run<AF_SLOTS>(lane, an, a1, o);
                         if (nx.total > 0) {
                             edge_loads(ed, an, nbase, o, nx, 0);
                             have = true;
@@ -1314,7 +1317,7 @@ int allegro_evaluate(mlp_model *m, mlp_nbr *g, hipStream_t s, double *energy, fl
         k.vec = a.chain_vec;
         k.U = base;
         k.G = g->G.as<float4>();
-        k.per_wg = ec_per_wg(n, E, d.rc, g->skin);
+        k.per_wg = ec_per_wg(n, E, d.rc, g->skin, AF_SLOTS);
         const int nb = nblk(n, k.per_wg);
         {
             ProfScope ps(PK_GEMM, s);

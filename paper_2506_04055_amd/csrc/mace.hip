@@ -527,6 +527,7 @@ __global__ void __launch_bounds__(256) k_mc_conv(const int *__restrict__ rowc, c
 // the sums in LDS, as the adjoint has it, took 4.3 + 1.4 ms on the first and
 // 0.065 + 0.026 on the second.
 // ---------------------------------------------------------------------------
+constexpr int MC_SLOTS = 6;   // atoms of a run (their dE/dA, 5 KB each, fill LDS)
 struct McEdgeArgs {
     const int *rowc, *colc, *zsp;
     const float4 *geom;
@@ -865,7 +866,7 @@ __global__ void __launch_bounds__(EC_THREADS) __attribute__((amdgpu_waves_per_eu
     // SiLU' of the first hidden layers waits in LDS for the way down (the
     // registers hold the last layer's; 16 per layer)
     constexpr int NPK = LAY == 0 ? 1 : 2;
-    __shared__ __attribute__((aligned(16))) float ys[EC_ROWS * 16], eg[EC_ROWS * 8], ga[EC_SLOTS * NF];
+    __shared__ __attribute__((aligned(16))) float ys[EC_ROWS * 16], eg[EC_ROWS * 8], ga[MC_SLOTS * NF];
     __shared__ v4f park[NPK * 4 * EC_THREADS];
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4,
               row = 16 * w + (lane & 15);
@@ -881,20 +882,20 @@ __global__ void __launch_bounds__(EC_THREADS) __attribute__((amdgpu_waves_per_eu
     EcStream<P> st;
     st.start(wst, A.W);
     const float *er = eg + 8 * row, *yr = ys + 16 * row;
-    int base = A.rowc[a], off = ec_row_off(A.rowc, lane, a, a1) - base;
+    int base = A.rowc[a], off = ec_row_off<MC_SLOTS>(A.rowc, lane, a, a1) - base;
     McEdge ed;
     bool have = false;   // the run's first piece is in ed
     while (a < a1) {
         __syncthreads();   // the last reads of the previous run's LDS
-        const EcRun run = ec_run(lane, a, a1, off);
+        const EcRun run = ec_run<MC_SLOTS>(lane, a, a1, off);
         const int na = run.na, nch = run.nch, total = run.total;
-        const int an = min(a + na, a1), nbase = A.rowc[an], noff = ec_row_off(A.rowc, lane, an, a1);
+        const int an = min(a + na, a1), nbase = A.rowc[an], noff = ec_row_off<MC_SLOTS>(A.rowc, lane, an, a1);
         if (total > 0)   // dE/dA of the run's atoms, per degree [slot][c][path][k]
 #pragma unroll
             for (int L = 0; L < 4; L++) {
                 const int cnt = (2 * L + 1) * cp_nL(L, NP) * MK;
                 const float *src = A.A.p[L] + (long)a * cnt;
-                float *dst = ga + EC_SLOTS * mc_goff(L, NP);
+                float *dst = ga + MC_SLOTS * mc_goff(L, NP);
                 for (int q = 4 * tid; q < na * cnt; q += 4 * EC_THREADS)
                     *reinterpret_cast<v4f *>(dst + q) = *reinterpret_cast<const v4f *>(src + q) * A.scale;
             }
@@ -938,7 +939,7 @@ __global__ void __launch_bounds__(EC_THREADS) __attribute__((amdgpu_waves_per_eu
                     if constexpr (decltype(s)::value == 0) return o0;
                     else return o1;
                 });
-                const float *gp = ga + EC_SLOTS * mc_goff(L, NP) + slot * nc * ld + cp_loc(p) * MK + 4 * g;
+                const float *gp = ga + MC_SLOTS * mc_goff(L, NP) + slot * nc * ld + cp_loc(p) * MK + 4 * g;
                 auto dot4 = [](v4f x, v4f y, float s) MC_INLINE {
                     return fmaf(x[3], y[3], fmaf(x[2], y[2], fmaf(x[1], y[1], fmaf(x[0], y[0], s))));
                 };
@@ -1008,7 +1009,7 @@ __global__ void __launch_bounds__(EC_THREADS) __attribute__((amdgpu_waves_per_eu
                             *reinterpret_cast<v4f *>(A.MSG + (e * 4 + c) * MK + 16 * t + 4 * g) = gh[c][t];
             if (ch == nch - 1 && an < a1) {   // the next run's first edges
                 const int o = noff - nbase;
-                const EcRun nx = ec_run(lane, an, a1, o);
+                const EcRun nx = ec_run<MC_SLOTS>(lane, an, a1, o);
                 if (nx.total > 0) {
                     mc_edge_load<LAY>(ed, A, nbase, o, nx, 0);
                     have = true;
@@ -1893,7 +1894,7 @@ int mace_evaluate(mlp_model *m, mlp_nbr *g, hipStream_t s, double *energy, float
     ka.G = g->G.as<float4>();
     ka.n = n;
     ka.nd1 = nd1;
-    ka.per_wg = ec_per_wg(n, E, a.rc, g->skin);
+    ka.per_wg = ec_per_wg(n, E, a.rc, g->skin, MC_SLOTS);
     auto edges = [&](int t, bool fwd, int nd, const McBlk &A) {
         McEdgeArgs k = ka;
         k.nd = nd;

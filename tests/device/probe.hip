@@ -96,5 +96,9 @@ int probe_phase(const float *r, int n, float rc, float *o) {
     k_phase<<<(n + 255) / 256, 256>>>(r, n, th, thl, reinterpret_cast<float2 *>(o));
     return done();
 }
+// atoms per workgroup of the fused edge kernels (host)
+int probe_atoms_per_workgroup(long n, long n_edges_skin, float rc, float skin, int slots) {
+    return ec_per_wg(n, n_edges_skin, rc, skin, slots);
+}
 
 }  // extern "C"

@@ -2,14 +2,14 @@
 library): the rounding of the FP32 operand form, which adds up in the energy of
 a large system but hides in that of a small one."""
 import ctypes
-import os
 
 import numpy as np
 import pytest
 
+from paper_2506_04055_amd.build import probe_lib
+
 pytestmark = pytest.mark.gpu
 
-LIB = os.path.join(os.path.dirname(os.path.abspath(__file__)), "device", "libprobe.so")
 U = 2.0 ** -24
 
 
@@ -18,7 +18,7 @@ def probe():
     import torch
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
-    return ctypes.CDLL(LIB)
+    return ctypes.CDLL(probe_lib())
 
 
 def dev(a):
