@@ -559,4 +559,241 @@ int node_gemm_chain(hipStream_t s, int precision, const GemmChain &c) {
     return hipGetLastError() == hipSuccess ? 0 : -5;
 }
 
+// ---------------------------------------------------------------------------
+// A bias-free SiLU MLP over rows with every hidden layer kept on chip:
+//   forward  C = h_n Wo^T,  h_q = silu(h_(q-1) W_q^T),  h_0 = X
+//   adjoint  dE/dX from dE/dC, the hidden layers recomputed per tile and
+//            their pre-activations held in registers (in the MFMA output
+//            layout, so the SiLU' gates are elementwise on the accumulators)
+// Hidden widths are at most 16 HT (HT tiles, HT / 2 32-wide k-blocks; this
+// build instantiates HT = 4, widths up to 64), the input at most 32 wide.  Each
+// wave owns 16 rows; the tile parked in LDS between layers becomes the next
+// product's A operand.  Every row is an edge, so what it costs goes with the
+// edges alone (MACE's systems of few neighbours: mc_edge_kernels in mace.hip).
+// ---------------------------------------------------------------------------
+#ifndef MLP_GW
+#define MLP_GW 4
+#endif
+constexpr int MG = MLP_GW;   // waves per workgroup of the fused MLP kernels (rows 16 MG per workgroup;
+                             // eight measured slower than four on MACE's radial MLPs)
+template <int P>
+struct MlpLds {
+    static constexpr int C_BYTES = MG * 16 * LDC * 4;
+    static constexpr int BYTES = GemmLds<P>::B_BYTES > C_BYTES ? GemmLds<P>::B_BYTES : C_BYTES;
+};
+
+template <int P, int HT>
+__device__ __forceinline__ void silu_tile(float *ct, int N) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int it = 0; it < EIT; it++) {
+        const int idx = lane + 64 * it, row = idx / (NCH / 4), c4 = 4 * (idx % (NCH / 4));
+        if (c4 >= 16 * HT) continue;
+        v4f *p = reinterpret_cast<v4f *>(ct + row * LDC + c4);
+        *p = c4 < N ? silu4(*p) : v4f{0.f, 0.f, 0.f, 0.f};
+    }
+    __builtin_amdgcn_wave_barrier();   // each wave reads back only its own tile
+}
+
+template <int P, int NH, int HT>
+__global__ void __launch_bounds__(64 * MG) __attribute__((amdgpu_waves_per_eu(2)))
+k_mlp_fwd(const float *__restrict__ X, int ldx, EdgeMlp W, float *__restrict__ C, int ldc, int M, const int *Mc) {
+    __shared__ __attribute__((aligned(16))) char lds[MlpLds<P>::BYTES];
+    if (Mc) M = min(M, *Mc);
+    if ((long)blockIdx.x * MG * 16 >= M) return;   // the whole workgroup leaves
+    const int lane = threadIdx.x & 63, c16 = lane & 15, g = lane >> 4;
+    const long m0 = ((long)blockIdx.x * MG + (threadIdx.x >> 6)) * 16;
+    const long arow = m0 + c16;
+    const bool rowok = arow < M;
+    const float *Xr = X + (rowok ? arow : 0) * (long)ldx;
+    constexpr int KH = HT / 2;
+    AOp<P, KH> a;
+    {
+        const int K0 = W.f[0].K;
+        AOp<P, 1> x;
+        x.load(g, [&](int k) {
+            v4f z;
+#pragma unroll
+            for (int q = 0; q < 4; q++) z[q] = (rowok && k + q < K0) ? Xr[k + q] : 0.f;
+            return z;
+        });
+        v4f acc[HT];
+#pragma unroll
+        for (int t = 0; t < HT; t++) acc[t] = v4f{0.f, 0.f, 0.f, 0.f};
+        mma_pass<P, 1, HT, MG>(lds, W.f[0], 0, K0, x, acc);
+        float *ct = park_tile<HT>(lds, acc);
+        silu_tile<P, HT>(ct, W.f[0].N);
+        a.load(g, [&](int k) { return *reinterpret_cast<const v4f *>(ct + c16 * LDC + k); });
+    }
+#pragma unroll
+    for (int q = 1; q < NH; q++) {
+        v4f acc[HT];
+#pragma unroll
+        for (int t = 0; t < HT; t++) acc[t] = v4f{0.f, 0.f, 0.f, 0.f};
+        mma_pass<P, KH, HT, MG>(lds, W.f[q], 0, W.f[q].K, a, acc);
+        float *ct = park_tile<HT>(lds, acc);
+        silu_tile<P, HT>(ct, W.f[q].N);
+        a.load(g, [&](int k) { return *reinterpret_cast<const v4f *>(ct + c16 * LDC + k); });
+    }
+    const PackedW &Wo = W.f[NH];
+    for (int n0 = 0; n0 < Wo.N; n0 += NCH) {
+        const int ncols = min(NCH, Wo.N - n0);
+        v4f acc[CT];
+#pragma unroll
+        for (int t = 0; t < CT; t++) acc[t] = v4f{0.f, 0.f, 0.f, 0.f};
+        mma_pass<P, KH, CT, MG>(lds, Wo, n0, Wo.K, a, acc);
+        const float *ct = park_tile(lds, acc);
+#pragma unroll
+        for (int it = 0; it < EIT; it++) {
+            const int idx = lane + 64 * it, row = idx / (NCH / 4), c4 = 4 * (idx % (NCH / 4));
+            const long m = m0 + row;
+            if (m >= M || c4 >= ncols) continue;
+            *reinterpret_cast<v4f *>(C + m * ldc + n0 + c4) = *reinterpret_cast<const v4f *>(ct + row * LDC + c4);
+        }
+    }
+}
+
+// acc *= SiLU'(pre), elementwise in the MFMA output layout
+template <int HT>
+__device__ __forceinline__ void dsilu_acc(v4f *acc, const v4f *pre) {
+#pragma unroll
+    for (int t = 0; t < HT; t++) acc[t] = dsilu4(acc[t], pre[t]);
+}
+
+template <int P, int NH, int HT, int KSG>
+__global__ void __launch_bounds__(64 * MG) __attribute__((amdgpu_waves_per_eu(2)))
+k_mlp_bwd(const float *__restrict__ X, int ldx, EdgeMlp W, const float *__restrict__ GC, int ldgc, float *GX,
+          int ldgx, int add, int M, const int *Mc) {
+    __shared__ __attribute__((aligned(16))) char lds[MlpLds<P>::BYTES];
+    if (Mc) M = min(M, *Mc);
+    if ((long)blockIdx.x * MG * 16 >= M) return;
+    const int lane = threadIdx.x & 63, c16 = lane & 15, g = lane >> 4;
+    const long m0 = ((long)blockIdx.x * MG + (threadIdx.x >> 6)) * 16;
+    const long arow = m0 + c16;
+    const bool rowok = arow < M;
+    constexpr int KH = HT / 2;
+    // dE/dC of the wave's rows, loaded first so that its latency overlaps the recompute
+    AOp<P, KSG> ga;
+    {
+        const float *Gr = GC + (rowok ? arow : 0) * (long)ldgc;
+        const int NO = W.f[NH].N;
+        ga.load_row(g, Gr, NO, rowok);
+    }
+    // forward recompute: pre-activations of every hidden layer
+    v4f pre[NH][HT];
+    AOp<P, KH> a;
+    {
+        const float *Xr = X + (rowok ? arow : 0) * (long)ldx;
+        const int K0 = W.f[0].K;
+        AOp<P, 1> x;
+        x.load(g, [&](int k) {
+            v4f z;
+#pragma unroll
+            for (int q = 0; q < 4; q++) z[q] = (rowok && k + q < K0) ? Xr[k + q] : 0.f;
+            return z;
+        });
+#pragma unroll
+        for (int t = 0; t < HT; t++) pre[0][t] = v4f{0.f, 0.f, 0.f, 0.f};
+        mma_pass<P, 1, HT, MG>(lds, W.f[0], 0, K0, x, pre[0]);
+    }
+#pragma unroll
+    for (int q = 1; q < NH; q++) {
+        float *ct = park_tile<HT>(lds, pre[q - 1]);
+        silu_tile<P, HT>(ct, W.f[q - 1].N);
+        a.load(g, [&](int k) { return *reinterpret_cast<const v4f *>(ct + c16 * LDC + k); });
+#pragma unroll
+        for (int t = 0; t < HT; t++) pre[q][t] = v4f{0.f, 0.f, 0.f, 0.f};
+        mma_pass<P, KH, HT, MG>(lds, W.f[q], 0, W.f[q].K, a, pre[q]);
+    }
+    // dE/dh of the last hidden layer through the output matrix, then down
+    v4f acc[HT];
+#pragma unroll
+    for (int t = 0; t < HT; t++) acc[t] = v4f{0.f, 0.f, 0.f, 0.f};
+    mma_pass<P, KSG, HT, MG>(lds, W.a[NH], 0, W.a[NH].K, ga, acc);
+    dsilu_acc<HT>(acc, pre[NH - 1]);
+#pragma unroll
+    for (int q = NH - 1; q >= 1; q--) {
+        float *ct = park_tile<HT>(lds, acc);
+        __builtin_amdgcn_wave_barrier();
+        a.load(g, [&](int k) { return *reinterpret_cast<const v4f *>(ct + c16 * LDC + k); });
+#pragma unroll
+        for (int t = 0; t < HT; t++) acc[t] = v4f{0.f, 0.f, 0.f, 0.f};
+        mma_pass<P, KH, HT, MG>(lds, W.a[q], 0, W.a[q].K, a, acc);
+        dsilu_acc<HT>(acc, pre[q - 1]);
+    }
+    // dE/dX = dE/dP_0 W_0 (at most 16 columns)
+    float *ct = park_tile<HT>(lds, acc);
+    __builtin_amdgcn_wave_barrier();
+    a.load(g, [&](int k) { return *reinterpret_cast<const v4f *>(ct + c16 * LDC + k); });
+    v4f gx[1] = {v4f{0.f, 0.f, 0.f, 0.f}};
+    mma_pass<P, KH, 1, MG>(lds, W.a[0], 0, W.a[0].K, a, gx);
+    const float *cx = park_tile<1>(lds, gx);
+    const int NX = W.a[0].N;
+    // 16 rows x 16 columns: lane (row, 4-column group) = (lane / 4, lane % 4)
+    const int row = lane >> 2, c4 = 4 * (lane & 3);
+    const long m = m0 + row;
+    if (m < M && c4 < NX) {
+        v4f o = *reinterpret_cast<const v4f *>(cx + row * LDC + c4);
+        float *d = GX + m * ldgx + c4;
+        if (add) o += gld4(d);
+        *reinterpret_cast<v4f *>(d) = o;
+    }
+}
+
+template <int P, int NH, int HT>
+static int mlp_fwd_launch(hipStream_t s, const EdgeMlp &W, const float *X, int ldx, float *C, int ldc, int M,
+                          const int *Mc) {
+    const unsigned bx = (unsigned)((M + 16 * MG - 1) / (16 * MG));
+    k_mlp_fwd<P, NH, HT><<<bx, 64 * MG, 0, s>>>(X, ldx, W, C, ldc, M, Mc);
+    return 0;
+}
+
+template <int P, int NH, int HT, int KSG>
+static int mlp_bwd_launch(hipStream_t s, const EdgeMlp &W, const float *X, int ldx, const float *GC, int ldgc,
+                          float *GX, int ldgx, bool add, int M, const int *Mc) {
+    const unsigned bx = (unsigned)((M + 16 * MG - 1) / (16 * MG));
+    k_mlp_bwd<P, NH, HT, KSG><<<bx, 64 * MG, 0, s>>>(X, ldx, W, GC, ldgc, GX, ldgx, add ? 1 : 0, M, Mc);
+    return 0;
+}
+
+static bool mlp_shape_ok(const EdgeMlp &W, int *HT) {
+    if (W.nh != 3 || W.f[0].K > 32 || W.a[0].N > 16) return false;
+    for (int q = 0; q < W.nh; q++)
+        if (W.f[q].N > 64) return false;
+    *HT = 4;
+    return W.f[W.nh].N <= 384;
+}
+
+int edge_mlp_forward(hipStream_t s, int precision, const EdgeMlp &W, const float *X, int ldx, float *C, int ldc,
+                     int M, const int *Mc) {
+    int HT;
+    if (M <= 0) return 0;
+    if (!mlp_shape_ok(W, &HT)) return -1;
+#define MF(P_) mlp_fwd_launch<P_, 3, 4>(s, W, X, ldx, C, ldc, M, Mc)
+    if (precision == 0) MF(0);
+    else if (precision == 1) MF(1);
+    else MF(2);
+#undef MF
+    return hipGetLastError() == hipSuccess ? 0 : -5;
+}
+
+int edge_mlp_adjoint(hipStream_t s, int precision, const EdgeMlp &W, const float *X, int ldx, const float *GC,
+                     int ldgc, float *GX, int ldgx, bool add, int M, const int *Mc) {
+    int HT;
+    if (M <= 0) return 0;
+    if (!mlp_shape_ok(W, &HT)) return -1;
+    const int NO = W.f[W.nh].N;
+#define MB2(P_, HT_)                                                                                          \
+    (NO <= 128 ? mlp_bwd_launch<P_, 3, HT_, 4>(s, W, X, ldx, GC, ldgc, GX, ldgx, add, M, Mc)                    \
+               : (NO <= 256 ? mlp_bwd_launch<P_, 3, HT_, 8>(s, W, X, ldx, GC, ldgc, GX, ldgx, add, M, Mc)       \
+                            : mlp_bwd_launch<P_, 3, HT_, 12>(s, W, X, ldx, GC, ldgc, GX, ldgx, add, M, Mc)))
+#define MB(P_) MB2(P_, 4)
+    if (precision == 0) MB(0);
+    else if (precision == 1) MB(1);
+    else MB(2);
+#undef MB
+#undef MB2
+    return hipGetLastError() == hipSuccess ? 0 : -5;
+}
+
 }  // namespace mlp

@@ -239,7 +239,7 @@ int mace_create(mlp_model *m, const McDims &d, const float *weights, size_t n_we
 void mace_destroy(mlp_model *m);
 int mace_evaluate(mlp_model *m, mlp_nbr *g, hipStream_t s, double *energy, float *forces_user,
                   float *atom_energy_user, int n_seg, const int *seg_dev);
-size_t mace_arena_bytes(const mlp_model *m, long n_atoms, long n_edges, bool counted = false);
+size_t mace_arena_bytes(const mlp_model *m, long n_atoms, long n_edges, float skin, bool counted = false);
 // Fill m->phi0_dev (device, S x 3F) from the embedding and the first layer's
 // message MLP, in the model's precision; tmp: device scratch of 2 S F floats.
 int first_layer_table(mlp_model *m, hipStream_t s, float *tmp);

@@ -34,8 +34,10 @@
 //   P(l1, l2 -> lambda) = sum_ab G A'_l1a A'_l2b of a channel are formed once
 //   in registers and serve both the two-body paths and, coupled with one
 //   more A', the three-body paths.
-// Radial MLPs of other depths or widths take a kernel per step: the MLP as
-// GEMMs over edges, then the convolution with one half-wave per atom:
+// Systems of few neighbours per atom (mc_edge_kernels) have the radial MLP in
+// one kernel and the convolution in another, radial MLPs of other depths or
+// widths a kernel per step: the MLP as GEMMs over edges, then the convolution
+// with one half-wave per atom:
 // * the l2 = 1 conv paths accumulate per atom the moments
 //   M_p[a][b] = sum_e R_e,p Y_l1a hb_j,1b and couple them once per atom
 //   (A_p,c = sum_ab G[a][b][c] M_p[a][b]); the adjoint contracts G with the
@@ -377,6 +379,7 @@ struct McModel {
     float *dev = nullptr;     // weights, transposed copies, tables (device)
     void *pk_dev = nullptr;   // packed GEMM operands
     PackedW radF[2][5], radA[2][5], waF[2][4], waA[2][4];
+    EdgeMlp rmlp[2];          // the radial MLPs as kernels of their own
     bool fused = false;       // the radial MLP and the convolution in one kernel each way
     char *chain = nullptr;    // its weights in the order of use
     size_t chF[2] = {}, chB[2] = {};
@@ -1536,7 +1539,20 @@ struct McArena {
     long X0, Y, P[2][4], A[2][4], R[2], GY, GX0, MSG, AR[2], AP[2], GAP, H1, HB1, H2, GH1S, U, EP, total;
 };
 
-static McArena mc_layout(const McModel &a, long N, long E, bool counted = false) {
+// Whether a system takes the edge kernels.  They cost 57 ns per atom (FP32: 73)
+// up to some 15 neighbours, however few there are: one atom fills a wave's 16
+// rows, six a run's 128.  With a kernel for the radial MLP and one for the
+// convolution an atom costs 18 ns and an edge 3.8 (20 and 4.9), and their ten
+// more launches 40 us.  Gases of 200,000 atoms with 1, 4, 8 and 10 neighbours,
+// split bf16: 9.2, 11.3, 11.5 and 11.6 ms with the edge kernels, 4.2, 6.3, 9.5
+// and 11.1 without; of 3,000 atoms with 4 and 6 neighbours 273 and 276 us
+// against 255 and 285.
+static bool mc_edge_kernels(const McModel &a, long N, long E, float skin) {
+    const double x = a.rc / (a.rc + skin), deg = N > 0 ? E * x * x * x / (double)N : 0.0;
+    return a.fused && deg >= 11.0 - 1.5e4 / (double)N;
+}
+
+static McArena mc_layout(const McModel &a, long N, long E, bool edge_kernels) {
     McArena L;
     long o = 0;
     auto take = [&](long cnt) {
@@ -1544,9 +1560,9 @@ static McArena mc_layout(const McModel &a, long N, long E, bool counted = false)
         o += (cnt + 63) / 64 * 64;
         return r;
     };
-    // the edge kernels keep MSG alone per edge; limits also count what passes
-    // between the convolution's steps (internal.h)
-    const long Eh = a.fused ? 0 : E, Es = counted ? E : Eh;
+    // the edge kernels keep MSG alone per edge; between a radial MLP's kernel and
+    // the convolution passes more, and its hidden layers where it takes several
+    const long Eh = a.fused ? 0 : E, Es = edge_kernels ? 0 : E;
     L.X0 = take(Es * a.NBP);
     L.Y = take(Es * 16);
     for (int t = 0; t < 2; t++) {
@@ -1575,8 +1591,9 @@ static McArena mc_layout(const McModel &a, long N, long E, bool counted = false)
     return L;
 }
 
-size_t mace_arena_bytes(const mlp_model *m, long n_atoms, long n_edges, bool counted) {
-    return (size_t)mc_layout(*m->mc, n_atoms, n_edges, counted).total * sizeof(float);
+size_t mace_arena_bytes(const mlp_model *m, long n_atoms, long n_edges, float skin, bool counted) {
+    const McModel &a = *m->mc;
+    return (size_t)mc_layout(a, n_atoms, n_edges, !counted && mc_edge_kernels(a, n_atoms, n_edges, skin)).total * sizeof(float);
 }
 
 // The weights of the edge kernels, where the radial MLP fits them: three
@@ -1756,8 +1773,7 @@ int mace_create(mlp_model *m, const McDims &d, const float *w, size_t n_weights)
     a->w_r2 = dev + oWr2;
     k_mc_species<<<nblk((long)S * K, 256), 256>>>(S, dev + oEmb, dev + oUp[0][0], dev + oSc[0], dev + oHb0,
                                                    dev + oSkip0);
-    // GEMM operands: radial matrices (where the edge kernels do not take
-    // them) and W_A, forward and adjoint
+    // GEMM operands: radial matrices and W_A, forward and adjoint
     struct Item {
         const float *W;
         int R, C;
@@ -1772,7 +1788,7 @@ int mace_create(mlp_model *m, const McDims &d, const float *w, size_t n_weights)
     std::vector<Item> items;
     for (int t = 0; t < 2; t++) {
         int prev = NB;
-        for (int q = 0; q <= d.nrad && !a->fused; q++) {
+        for (int q = 0; q <= d.nrad; q++) {
             const int rows = q < d.nrad ? d.rh[q] : NPt[t] * K;
             items.push_back({dev + oRad[t][q], rows, prev, false, &a->radF[t][q]});
             items.push_back({dev + oRad[t][q], rows, prev, true, &a->radA[t][q]});
@@ -1800,6 +1816,13 @@ int mace_create(mlp_model *m, const McDims &d, const float *w, size_t n_weights)
         hipFree(dev);
         delete a;
         return fail(rc, "mace: weight packing failed");
+    }
+    for (int t = 0; t < 2; t++) {
+        a->rmlp[t].nh = d.nrad;
+        for (int q = 0; q <= d.nrad; q++) {
+            a->rmlp[t].f[q] = a->radF[t][q];
+            a->rmlp[t].a[q] = a->radA[t][q];
+        }
     }
     m->mc = a;
     return 0;
@@ -1847,9 +1870,10 @@ int mace_evaluate(mlp_model *m, mlp_nbr *g, hipStream_t s, double *energy, float
     const int n = g->n_atoms, P = node_operands(m->precision), T = 2;
     const long E = g->n_edges_skin;
     int rc;
-    if ((rc = g->act.ensure(mace_arena_bytes(m, n, E), 1.2, &g->n_grows))) return rc;
+    if ((rc = g->act.ensure(mace_arena_bytes(m, n, E, g->skin), 1.2, &g->n_grows))) return rc;
     if ((rc = g->G.ensure(sizeof(float4) * (size_t)E + 64, 1.2, &g->n_grows))) return rc;
-    const McArena L = mc_layout(a, n, E);
+    const bool fused = mc_edge_kernels(a, n, E, g->skin);
+    const McArena L = mc_layout(a, n, E, fused);
     float *base = g->act.as<float>();
     float *X0 = base + L.X0, *Y = base + L.Y, *GY = base + L.GY, *GX0 = base + L.GX0, *MSG = base + L.MSG,
           *H1 = base + L.H1, *HB1 = base + L.HB1, *H2 = base + L.H2, *GH1S = base + L.GH1S, *U = base + L.U;
@@ -1924,8 +1948,14 @@ int mace_evaluate(mlp_model *m, mlp_nbr *g, hipStream_t s, double *energy, float
 
     // forward
     k_mc_zero<<<nblk(n + 64, 256), 256, 0, s>>>(U, n + 64);
-    if (!a.fused) k_mc_edge<<<eg, 256, 0, s>>>(rowc, n, geom, a.NB, a.NBP, a.pe, a.rc, X0, Y);
-    for (int t = 0; t < 2 && !a.fused; t++) {
+    if (!fused) k_mc_edge<<<eg, 256, 0, s>>>(rowc, n, geom, a.NB, a.NBP, a.pe, a.rc, X0, Y);
+    for (int t = 0; t < 2 && !fused; t++) {
+        if (a.fused) {
+            ProfScope ps(PK_GEMM, s);
+            if (edge_mlp_forward(s, P, a.rmlp[t], X0, a.NBP, base + L.R[t], NPt[t] * MK, (int)E, t ? e1 : e0))
+                return fail(-5, "mace radial MLP failed");
+            continue;
+        }
         const float *in = X0;
         int ldin = a.NBP;
         for (int q = 0; q < a.nrad; q++) {
@@ -1961,7 +1991,7 @@ int mace_evaluate(mlp_model *m, mlp_nbr *g, hipStream_t s, double *energy, float
         const int nd = t ? nd1 : nd0;
         if (nd <= 0) continue;
         const McBlk &AR = t ? AR1 : AR0, &AP = t ? AP1 : AP0;
-        if (a.fused)
+        if (fused)
             edges(t, true, nd, AR);
         else if (t == 0)
             k_mc_conv<0><<<nblk(nd, APB), 256, 0, s>>>(rowc, colc, nd, Y, base + L.R[0], nullptr, zsp, a.hb0tab, scale,
@@ -2014,7 +2044,7 @@ int mace_evaluate(mlp_model *m, mlp_nbr *g, hipStream_t s, double *energy, float
         k_mc_node1_bwd<<<nblk(nd1, APB), 256, 0, s>>>(nd1, zsp, nb);
         // dE/dA (before the W_A mix) over the A blocks
         if ((rc = mix_wa(s, P, AR1, GAP, a.waA[1], 10, nd1, false))) return rc;
-        if (a.fused) edges(1, false, nd1, AR1);
+        if (fused) edges(1, false, nd1, AR1);
         else k_mc_conv1_bwd<<<nblk(nd1, APB), 256, 0, s>>>(rowc, colc, nd1, Y, base + L.R[1], HB1, scale, AR1, GY, MSG);
     }
     if (nd0 > 0) {
@@ -2025,12 +2055,12 @@ int mace_evaluate(mlp_model *m, mlp_nbr *g, hipStream_t s, double *energy, float
         nb.Wout[1] = a.Wout[0][1];
         k_mc_node0_bwd<<<nblk(nd0, APB), 256, 0, s>>>(nd0, zsp, nb);
         if ((rc = mix_wa(s, P, AR0, GAP, a.waA[0], 4, nd0, false))) return rc;
-        if (a.fused) edges(0, false, nd0, AR0);
+        if (fused) edges(0, false, nd0, AR0);
         else
             k_mc_conv0_bwd<<<nblk(nd0, APB), 256, 0, s>>>(rowc, colc, nd0, nd1, Y, base + L.R[0], zsp, a.hb0tab, scale,
                                                           AR0, GY);
     }
-    if (a.fused) {
+    if (fused) {
         HIP_TRY(hipGetLastError());
         return launch_forces(s, rowc, revc, g->G.as<float4>(), perm, n, forces_user);
     }
@@ -2038,6 +2068,12 @@ int mace_evaluate(mlp_model *m, mlp_nbr *g, hipStream_t s, double *energy, float
     // edges first (stored), then the second layer's added on its prefix
     for (int t = 0; t < 2; t++) {
         const int *cnt = t ? e1 : e0;
+        if (a.fused) {
+            ProfScope ps(PK_GEMM, s);
+            if (edge_mlp_adjoint(s, P, a.rmlp[t], X0, a.NBP, base + L.R[t], NPt[t] * MK, GX0, a.NBP, t != 0, (int)E, cnt))
+                return fail(-5, "mace radial MLP adjoint failed");
+            continue;
+        }
         const float *gin = base + L.R[t];
         int ldg = NPt[t] * MK;
         for (int q = a.nrad - 1; q >= 0; q--) {

@@ -347,7 +347,7 @@ int first_layer_factor(mlp_model *m) {
 void eval_model_needs(const mlp_model *m, const mlp_nbr *g, size_t *act, size_t *G, size_t *Gs) {
     const size_t ne = (size_t)g->n_edges_skin;
     if (m->al || m->mc) {
-        *act = m->al ? allegro_arena_bytes(m, g->n_atoms, (long)ne) : mace_arena_bytes(m, g->n_atoms, (long)ne);
+        *act = m->al ? allegro_arena_bytes(m, g->n_atoms, (long)ne) : mace_arena_bytes(m, g->n_atoms, (long)ne, g->skin);
         *G = sizeof(float4) * ne + 64;
         *Gs = 64;
         return;
@@ -360,7 +360,7 @@ void eval_model_needs(const mlp_model *m, const mlp_nbr *g, size_t *act, size_t 
 size_t counted_act_bytes(const mlp_model *m, const mlp_nbr *g) {
     const long N = g->n_atoms, ne = g->n_edges_skin, T = m->T, F = m->F;
     if (m->al) return allegro_arena_bytes(m, N, ne, true);
-    if (m->mc) return mace_arena_bytes(m, N, ne, true);
+    if (m->mc) return mace_arena_bytes(m, N, ne, g->skin, true);
     return (size_t)(N * F * (T * counted_layer(F) + 4 + counted_adjoint(F)) + N + 64 * (12 * T + 32) + 4096 + QUEUE_INTS +
                     2 * energy_part_doubles(N)) * sizeof(float);
 }

@@ -47,7 +47,7 @@ int node_forward(hipStream_t, int, int, const NodeArgs &) { return node(); }
 int node_adjoint(hipStream_t, int, int, const NodeArgs &) { return node(); }
 int node_last(hipStream_t, int, int, const NodeArgs &) { return node(); }
 size_t allegro_arena_bytes(const mlp_model *, long, long, bool) { return 0; }
-size_t mace_arena_bytes(const mlp_model *, long, long, bool) { return 0; }
+size_t mace_arena_bytes(const mlp_model *, long, long, float, bool) { return 0; }
 int allegro_evaluate(mlp_model *, mlp_nbr *, hipStream_t, double *, float *, float *, int, const int *) { return 0; }
 int mace_evaluate(mlp_model *, mlp_nbr *, hipStream_t, double *, float *, float *, int, const int *) { return 0; }
 }  // namespace mlp

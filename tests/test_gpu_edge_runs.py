@@ -64,3 +64,16 @@ def run(mlp, label, oracle, hw, s, precision):
 def test_allegro_runs(mlp, n, degree, dense, precision):
     run(mlp, f"allegro mixed {degree}", AO, synth.make_allegro_weights(2, seed=12, bias_scale=0.1),
         mixed(n, degree, dense, 21), precision)
+
+
+# few neighbours: a kernel each for the radial MLP and the convolution (the first two), otherwise the edge kernels
+@pytest.mark.parametrize("n,degree,dense", [(2500, 1.0, 0), (6000, 2.0, 300), (2500, 9.0, 300)])
+@pytest.mark.parametrize("precision", ["fp32", "bf16", "bf16_node"])
+def test_mace_routes(mlp, n, degree, dense, precision):
+    import torch
+    d = run(mlp, f"mace mixed {degree}", MO, synth.make_mace_weights(2, seed=12, bias_scale=0.1),
+            mixed(n, degree, dense, 22), precision)
+    E = float(d.energy.item())
+    d.compute(forces=False)
+    torch.cuda.synchronize()
+    assert float(d.energy.item()) == E
