@@ -65,6 +65,22 @@ __global__ void k_phase(const float *__restrict__ r, int n, float th, float thl,
     if (i < n) ec_sincos_0pi(th, thl, r[i], o[i].x, o[i].y);
 }
 
+// The message pass or its adjoint with either form of the row offsets
+template <int P, int F, int K, bool WIDE>
+void message(int adjoint, const MsgArgs &a) {
+    if (adjoint)
+        k_msg_bwd_pw<P, F, K, WIDE><<<8, 64 * BWD_PIW_WAVES>>>(a.rowc, a.colc, a.geom, a.n, a.phi, a.v, a.gs1, a.gv1, a.A, a.c, a.rc, a.hop,
+                                                             a.hop_max, a.queue, a.gv_in, a.gphi, a.S);
+    else
+        k_msg_fwd_pw<P, F, K, WIDE><<<8, 64 * FWD_PIW_WAVES>>>(a.rowc, a.colc, a.geom, a.n, a.phi, a.u, a.s, a.v, a.A, a.c, a.rc, a.hop,
+                                                             a.hop_max, a.queue, a.sn, a.v1);
+}
+// byte offsets of (row, element) pairs in a row-major array, in the 32-bit form
+__global__ void k_row_offset(const int *__restrict__ row, const int *__restrict__ f, int n, int ld, unsigned long long *__restrict__ o) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) o[i] = RowAt<false>(row[i], ld, f[i]).o;
+}
+
 }  // namespace
 
 namespace mlp {
@@ -99,6 +115,24 @@ int probe_phase(const float *r, int n, float rc, float *o) {
 // atoms per workgroup of the fused edge kernels (host)
 int probe_atoms_per_workgroup(long n, long n_edges_skin, float rc, float skin, int slots) {
     return ec_per_wg(n, n_edges_skin, rc, skin, slots);
+}
+int probe_wide(long n, int F) { return msg_wide(n, F); }
+int probe_row_offset(const int *row, const int *f, int n, int ld, unsigned long long *o) {
+    k_row_offset<<<(n + 255) / 256, 256>>>(row, f, n, ld, o);
+    return done();
+}
+// in: rowc colc geom phi u s v gs1 gv1 A c hop; out: forward sn v1, adjoint gv gphi S; queue zeroed
+int probe_message(int wide, int adjoint, int F, int n, float rc, int hop_max, const void *const *in, void *const *out, int *queue) {
+    MsgArgs a = {};
+    a.rowc = (const int *)in[0], a.colc = (const int *)in[1], a.geom = (const float4 *)in[2], a.n = n;
+    a.phi = (const float *)in[3], a.u = (const float *)in[4], a.s = (const float *)in[5], a.v = (const float *)in[6];
+    a.gs1 = (const float *)in[7], a.gv1 = (const float *)in[8], a.A = (const float *)in[9], a.c = (const float *)in[10];
+    a.hop = (const int8_t *)in[11], a.hop_max = hop_max, a.rc = rc, a.queue = queue;
+    a.sn = (float *)out[0], a.v1 = (float *)out[1];
+    a.gv_in = (float *)out[0], a.gphi = (float *)out[1], a.S = (float4 *)out[2];
+    if (F == 64) wide ? message<2, 64, 8, true>(adjoint, a) : message<2, 64, 8, false>(adjoint, a);
+    else wide ? message<0, 128, 20, true>(adjoint, a) : message<0, 128, 20, false>(adjoint, a);
+    return done();
 }
 
 }  // extern "C"

@@ -103,3 +103,52 @@ def test_edge_phase(probe, rc):
     # no offset beyond the series' truncation (2e-9); the series' last sums and the result are rounded once each
     assert abs(err.mean(0)).max() <= 2.5e-9
     assert abs(err).max() <= 2 * U
+
+
+@pytest.mark.parametrize("F", [64, 128])
+def test_row_offsets_at_their_limit(probe, F):
+    """The largest system whose rows are reached by 32-bit offsets, and the first that is not."""
+    probe.probe_wide.argtypes = [ctypes.c_long, ctypes.c_int]
+    n = (2 ** 32 - 1) // (12 * F)
+    assert n < 2 ** 24 and not probe.probe_wide(n, F) and probe.probe_wide(n + 1, F)
+    assert probe.probe_wide(2 ** 24, 16) and not probe.probe_wide(2 ** 24 - 1, 16)
+    rng = np.random.default_rng(1)
+    for ld in (F, 3 * F):
+        row = np.concatenate([[0, n - 1], rng.integers(0, n, 10000)]).astype(np.int32)
+        f = np.concatenate([[0, ld - 1], rng.integers(0, ld, 10000)]).astype(np.int32)
+        R, Fe, O = dev(row), dev(f), dev(np.zeros(row.size, np.int64))
+        print(f"[case] row offsets F={F} ld={ld}", flush=True)
+        assert probe.probe_row_offset(ptr(R), ptr(Fe), row.size, ld, ptr(O)) == 0
+        want = 4 * (row.astype(np.int64) * ld + f)
+        assert want.max() < 2 ** 32 and np.array_equal(O.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("F,K", [(64, 8), (128, 20)])
+@pytest.mark.parametrize("adjoint", [0, 1])
+def test_message_rows_by_either_offset(probe, F, K, adjoint):
+    import torch
+    n, rc = 173, 5.0
+    rng = np.random.default_rng(2)
+    deg = rng.integers(0, 70, n)
+    deg[:3] = [0, 16, 70]
+    rowc = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    E = int(rowc[-1])
+    r = rng.uniform(1.0, rc, E)
+    d = rng.normal(size=(E, 3))
+    geom = np.concatenate([d / np.linalg.norm(d, axis=1, keepdims=True) * r[:, None], r[:, None]], 1).astype(np.float32)
+    rows = lambda *shape: rng.normal(size=shape).astype(np.float32)  # noqa: E731
+    host = [rowc, rng.integers(0, n, E).astype(np.int32), geom, rows(n, 3 * F), rows(n, 3 * F), rows(n, F), rows(n, 3 * F),
+            rows(n, F), rows(n, 3 * F), rows(3 * F, K), rows(3 * F), rng.integers(0, 3, n).astype(np.int8)]
+    data = [dev(h) for h in host]
+    ins = (ctypes.c_void_p * len(data))(*[t.data_ptr() for t in data])
+    res = []
+    for wide in (0, 1):
+        out = [torch.zeros(n, 3 * F, device="cuda"), torch.zeros(n, 3 * F, device="cuda"), torch.zeros(E, 4, device="cuda")]
+        outs = (ctypes.c_void_p * 3)(*[t.data_ptr() for t in out])
+        queue = torch.zeros(2048, dtype=torch.int32, device="cuda")
+        torch.cuda.synchronize()
+        print(f"[case] message F={F} adjoint={adjoint} wide={wide}", flush=True)
+        assert probe.probe_message(wide, adjoint, F, n, ctypes.c_float(rc), 1, ins, outs, ptr(queue)) == 0
+        res.append([t.cpu().numpy() for t in out])
+    assert all(np.array_equal(a, b) for a, b in zip(*res))
+    assert np.abs(res[0][1]).max() > 0 and (not adjoint or np.abs(res[0][2]).max() > 0)

@@ -42,11 +42,34 @@ def mixed(n_gas, degree, n_dense, seed):
     return synth.System(pos, rng.integers(0, 2, len(pos)).astype(np.int32), np.array([L] * 3), len(pos))
 
 
-def run(mlp, label, oracle, hw, s, precision):
+def copies_of(s, k):
+    """k^3 periodic copies; coordinates and box on a grid of 2^-14 A, so that every copy is exact in float32."""
+    assert k * max(s.box) < 512
+    q = 2.0 ** 14
+    sh = np.stack(np.meshgrid(*[np.arange(k)] * 3, indexing="ij"), -1).reshape(-1, 1, 3) * s.box
+    pos = (s.pos.astype(np.float64)[None] + sh).reshape(-1, 3)
+    assert np.array_equal(pos * q, np.round(pos * q))
+    return synth.System(pos.astype(np.float32), np.tile(s.species, k ** 3), s.box * k, s.n_atoms * k ** 3)
+
+
+def on_grid(s):
+    q = 2.0 ** 14
+    box = np.ceil(np.asarray(s.box, np.float64) * q) / q
+    pos = np.round(s.pos.astype(np.float64) * q) / q
+    pos[pos >= box] = 0
+    return synth.System(pos.astype(np.float32), s.species, box, s.n_atoms)
+
+
+def run(mlp, label, oracle, hw, s, precision, copies=1):
     import torch
     h, w = hw
-    print(f"[case] {label} {precision} n={s.n_atoms}", flush=True)
+    if copies > 1:
+        s = on_grid(s)
+    print(f"[case] {label} {precision} n={s.n_atoms} x {copies}^3", flush=True)
     E_ref, F_ref, U_ref = oracle.energy_forces(h, w, s.pos, s.species, s.box, per_atom=True)
+    if copies > 1:
+        s = copies_of(s, copies)
+        E_ref, F_ref, U_ref = E_ref * copies ** 3, np.tile(F_ref, (copies ** 3, 1)), np.tile(U_ref, copies ** 3)
     d = mlp.System(mlp.Model(h, w, precision), s.pos, s.species, s.box, skin=0.5)
     out = d.compute(atom_energy=True)
     torch.cuda.synchronize()
@@ -77,3 +100,29 @@ def test_mace_routes(mlp, n, degree, dense, precision):
     d.compute(forces=False)
     torch.cuda.synchronize()
     assert float(d.energy.item()) == E
+
+
+def _water():
+    return synth.water_box(4, 3.105, seed=7)
+
+
+def _fcc():
+    return synth.fcc_crystal(3, seed=6, sigma=0.1)
+
+
+def _mixed():
+    return mixed(300, 4.0, 250, 23)
+
+
+# several runs per workgroup by the plan (copies of one cell, so that the cell's oracle serves)
+@pytest.mark.parametrize("make,copies", [(_water, 5), (_fcc, 7), (_mixed, 6)])
+@pytest.mark.parametrize("precision", ["fp32", "bf16"])
+def test_allegro_large(mlp, make, copies, precision):
+    run(mlp, f"allegro {make.__name__}", AO, synth.make_allegro_weights(2, seed=12, bias_scale=0.1), make(), precision, copies)
+
+
+# more atoms per workgroup than waves in the forward, several runs per workgroup in the adjoint
+@pytest.mark.parametrize("make,copies", [(_water, 5), (_fcc, 7), (_mixed, 5)])
+@pytest.mark.parametrize("precision", ["fp32", "bf16"])
+def test_mace_large(mlp, make, copies, precision):
+    run(mlp, f"mace {make.__name__}", MO, synth.make_mace_weights(2, seed=12, bias_scale=0.1), make(), precision, copies)
