@@ -630,7 +630,7 @@ __global__ void __launch_bounds__(EC_THREADS) __attribute__((amdgpu_waves_per_eu
                 float u, du;
                 envelope(r / A.rc, A.p, u, du);
                 float s1, c1, Y[16];
-                ec_sincos_0pi(A.th, A.thl, r, s1, c1);
+                ec_sincos_0pi<P>(A.th, A.thl, r, s1, c1);
                 sh16(ed.gm.x * ir, ed.gm.y * ir, ed.gm.z * ir, Y);
 #pragma unroll
                 for (int k = 0; k < 4; k++)
@@ -769,13 +769,13 @@ __global__ void __launch_bounds__(EC_THREADS) __attribute__((amdgpu_waves_per_eu
             p1 = cbv(AF_B1, 0);
             ec_layer<U0, NS, 1, 1>(st, next, &p1, [&](auto) { return ec_op<P>(xa, xb); });
             p2 = cbv(AF_B2, 0);
-            ec_layer<U0 + 1, NS, 1, 1>(st, next, &p2, [&](auto) { return ec_op<P>(ec_act<D>(p1), z4); });
+            ec_layer<U0 + 1, NS, 1, 1>(st, next, &p2, [&](auto) { return ec_op<P>(ec_act<P, D>(p1), z4); });
             p3[0] = cbv(AF_B3, 0);
             p3[1] = cbv(AF_B3, 1);
-            ec_layer<U0 + 2, NS, 2, 1>(st, next, p3, [&](auto) { return ec_op<P>(ec_act<D>(p2), z4); });
+            ec_layer<U0 + 2, NS, 2, 1>(st, next, p3, [&](auto) { return ec_op<P>(ec_act<P, D>(p2), z4); });
 #pragma unroll
             for (int t = 0; t < 4; t++) y[t] = cbv(AF_B4, t);
-            ec_layer<U0 + 4, NS, 4, 1>(st, next, y, [&](auto) { return ec_op<P>(ec_act<D>(p3[0]), ec_act<D>(p3[1])); });
+            ec_layer<U0 + 4, NS, 4, 1>(st, next, y, [&](auto) { return ec_op<P>(ec_act<P, D>(p3[0]), ec_act<P, D>(p3[1])); });
         };
 
         // carried from phase to phase: x0 then dE/dx0, w0 then dE/dw0, we of
@@ -831,7 +831,7 @@ __global__ void __launch_bounds__(EC_THREADS) __attribute__((amdgpu_waves_per_eu
                     }
 #pragma unroll
                     for (int t = 0; t < 4; t++) M[t] = cbv(AF_L2, t);
-                    ec_layer<16, N2, 4, 2>(st, next, M, [&](auto s) { return ec_op<P>(ec_silu_d(PL[2 * s]), ec_silu_d(PL[2 * s + 1])); });
+                    ec_layer<16, N2, 4, 2>(st, next, M, [&](auto s) { return ec_op<P>(ec_silu_d<P>(PL[2 * s]), ec_silu_d<P>(PL[2 * s + 1])); });
                     const float u = er[1], gE = er[5];
 #pragma unroll
                     for (int t = 0; t < 4; t++) sA[t] = (M[t] * u + sA[t]) * r2;   // x1
@@ -840,7 +840,7 @@ __global__ void __launch_bounds__(EC_THREADS) __attribute__((amdgpu_waves_per_eu
                     float d2 = 0.f;
 #pragma unroll
                     for (int t = 0; t < 2; t++) {
-                        const v4f w2 = cbv(AF_W2, t), h = ec_silu_d(PO[t]);
+                        const v4f w2 = cbv(AF_W2, t), h = ec_silu_d<P>(PO[t]);
 #pragma unroll
                         for (int k = 0; k < 4; k++) d2 = fmaf(w2[k], h[k], d2);
                         PO[t] *= w2 * (gE * u);

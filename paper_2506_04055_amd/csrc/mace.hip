@@ -583,7 +583,7 @@ __device__ __forceinline__ void mc_edge_load(McEdge &E, const McEdgeArgs &A, int
         E.j = A.colc[e];
     }
 }
-template <int LAY>
+template <int P, int LAY>
 __device__ __forceinline__ void mc_edge_put(const McEdge &E, const McEdgeArgs &A, float *ys, float *eg) {
     typedef ec_v4f v4f;
     if (threadIdx.x < EC_ROWS) {
@@ -591,7 +591,7 @@ __device__ __forceinline__ void mc_edge_put(const McEdge &E, const McEdgeArgs &A
         const float r = E.gm.w, ir = 1.0f / r;
         float u, du, s1, c1, Y[16];
         envelope(r / A.rc, A.pe, u, du);
-        ec_sincos_0pi(A.th, A.thl, r, s1, c1);
+        ec_sincos_0pi<P>(A.th, A.thl, r, s1, c1);
         sh16(E.gm.x * ir, E.gm.y * ir, E.gm.z * ir, Y);
         // rows past the end carry nothing: u = 0 (no MLP has a bias)
 #pragma unroll
@@ -627,8 +627,8 @@ __device__ __forceinline__ void mc_hidden(EcStream<P> &st, const char *next, con
 #pragma unroll
     for (int t = 0; t < 4; t++) p1[t] = p2[t] = p3[t] = z4;
     ec_layer<U0, NS, 4, 1>(st, next, p1, [&](auto) { return ec_op<P>(x, z4); });
-    ec_layer<U0 + 4, NS, 4, 2>(st, next, p2, [&](auto s) { return ec_op<P>(ec_silu_d(p1[2 * s]), ec_silu_d(p1[2 * s + 1])); });
-    ec_layer<U0 + 12, NS, 4, 2>(st, next, p3, [&](auto s) { return ec_op<P>(ec_silu_d(p2[2 * s]), ec_silu_d(p2[2 * s + 1])); });
+    ec_layer<U0 + 4, NS, 4, 2>(st, next, p2, [&](auto s) { return ec_op<P>(ec_silu_d<P>(p1[2 * s]), ec_silu_d<P>(p1[2 * s + 1])); });
+    ec_layer<U0 + 12, NS, 4, 2>(st, next, p3, [&](auto s) { return ec_op<P>(ec_silu_d<P>(p2[2 * s]), ec_silu_d<P>(p2[2 * s + 1])); });
 }
 
 constexpr int mc_fwd_units(int lay) { return 20 + 4 * (lay == 0 ? 4 : 10); }
@@ -739,7 +739,7 @@ __global__ void __launch_bounds__(EC_THREADS) __attribute__((amdgpu_waves_per_eu
             const float r = gm.w, ir = 1.0f / r;
             float u, du, s1, c1, sk, ck;
             envelope(r / A.rc, A.pe, u, du);
-            ec_sincos_0pi(A.th, A.thl, r, s1, c1);
+            ec_sincos_0pi<P>(A.th, A.thl, r, s1, c1);
             ec_angle(g, s1, c1, sk, ck);
             // lanes past the atom's edges carry nothing (no MLP has a bias)
             const float bu = e + m < e1 ? A.c0 * ir * u : 0.f;
@@ -790,10 +790,10 @@ __global__ void __launch_bounds__(EC_THREADS) __attribute__((amdgpu_waves_per_eu
 #pragma unroll
             for (int t = 0; t < 4; t++) p1[t] = p2[t] = p3[t] = z4;
             ec_layer<0, NS, 4, 1>(st, A.W, p1, [&](auto) { return ec_op<P>(x, z4); });
-            ec_layer<4, NS, 4, 2>(st, A.W, p2, [&](auto s) { return ec_op<P>(ec_silu(p1[2 * s]), ec_silu(p1[2 * s + 1])); });
-            ec_layer<12, NS, 4, 2>(st, A.W, p3, [&](auto s) { return ec_op<P>(ec_silu(p2[2 * s]), ec_silu(p2[2 * s + 1])); });
-            o0 = ec_op<P>(ec_silu(p3[0]), ec_silu(p3[1]));
-            o1 = ec_op<P>(ec_silu(p3[2]), ec_silu(p3[3]));
+            ec_layer<4, NS, 4, 2>(st, A.W, p2, [&](auto s) { return ec_op<P>(ec_silu<P>(p1[2 * s]), ec_silu<P>(p1[2 * s + 1])); });
+            ec_layer<12, NS, 4, 2>(st, A.W, p3, [&](auto s) { return ec_op<P>(ec_silu<P>(p2[2 * s]), ec_silu<P>(p2[2 * s + 1])); });
+            o0 = ec_op<P>(ec_silu<P>(p3[0]), ec_silu<P>(p3[1]));
+            o1 = ec_op<P>(ec_silu<P>(p3[2]), ec_silu<P>(p3[3]));
         }
         float4 ngm = gm;
         int nj = j;
@@ -906,7 +906,7 @@ __global__ void __launch_bounds__(EC_THREADS) __attribute__((amdgpu_waves_per_eu
             if (nch > 1) __syncthreads();   // the last reads of the previous piece's rows
             if (!have) mc_edge_load<LAY>(ed, A, base, off, run, ch);
             have = false;
-            mc_edge_put<LAY>(ed, A, ys, eg);
+            mc_edge_put<P, LAY>(ed, A, ys, eg);
             __syncthreads();
             const int slot = __float_as_int(er[6]);
             const long e = base + ch * EC_ROWS + row;
@@ -928,8 +928,8 @@ __global__ void __launch_bounds__(EC_THREADS) __attribute__((amdgpu_waves_per_eu
                 park[t * EC_THREADS + tid] = p1[t];
                 if constexpr (NPK > 1) park[(4 + t) * EC_THREADS + tid] = p2[t];
             }
-            o0 = ec_op<P>(ec_silu_d(p3[0]), ec_silu_d(p3[1]));
-            o1 = ec_op<P>(ec_silu_d(p3[2]), ec_silu_d(p3[3]));
+            o0 = ec_op<P>(ec_silu_d<P>(p3[0]), ec_silu_d<P>(p3[1]));
+            o1 = ec_op<P>(ec_silu_d<P>(p3[2]), ec_silu_d<P>(p3[3]));
             float Y[16], gy[16];
             load16(yr, Y);
 #pragma unroll

@@ -55,14 +55,14 @@ __global__ void k_sigmoid(const float *__restrict__ x, int n, float4 *__restrict
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     ec_v4f v = {x[i], 0.f, 0.f, 0.f};
-    const ec_v4f s = ec_silu_d(v);
-    o[i] = make_float4(1.0f + __expf(-x[i]), ec_sigmoid(x[i]), s[0], v[0]);
+    const ec_v4f s = ec_silu_d<0>(v);
+    o[i] = make_float4(1.0f + __expf(-x[i]), ec_sigmoid<0>(x[i]), s[0], v[0]);
 }
 
 // sin and cos of pi r / rc as the edge chains take them
 __global__ void k_phase(const float *__restrict__ r, int n, float th, float thl, float2 *__restrict__ o) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) ec_sincos_0pi(th, thl, r[i], o[i].x, o[i].y);
+    if (i < n) ec_sincos_0pi<0>(th, thl, r[i], o[i].x, o[i].y);
 }
 
 // The message pass or its adjoint with either form of the row offsets
