@@ -136,7 +136,9 @@ const char *mlp_last_error(void);
  * precision: the operand forms of the two matrix-core contractions, the
  *   node-feature GEMMs (node) and the radial filter of the message kernels
  *   (filter):
- *   MLP_FP32         node FP32, filter FP32 (v_mfma_f32_16x16x4_f32);
+ *   MLP_FP32         node and filter FP32, every operand as three bfloat16
+ *                    parts (24 bits), six products per tile
+ *                    (v_mfma_f32_16x16x32_bf16);
  *   MLP_BF16         node and filter split bfloat16 ("bf16x3"): x = hi + lo,
  *                    three bf16 products per tile (v_mfma_f32_16x16x32_bf16),
  *                    about 16 significant bits per operand;
@@ -146,7 +148,9 @@ const char *mlp_last_error(void);
  *                    FP32 accumulation, everything else FP32;
  *   MLP_BF16_NODE_X3 node plain bfloat16, filter split bfloat16.
  *   Accumulation is FP32 in every mode; geometry, cutoff envelope, message
- *   and force accumulation stay FP32; the energy sum is FP64.
+ *   and force accumulation stay FP32; the energy sum is FP64.  An operand
+ *   beyond bfloat16's largest number (3.389e38), or infinite, has no second
+ *   part: the outputs that depend on it are NaN, those of other atoms are not.
  * Errors: INVALID_ARG (header or weight count), OOM, DEVICE.
  * ------------------------------------------------------------------------- */
 int mlp_model_create(const char *header_json, const float *weights, size_t n_weights,

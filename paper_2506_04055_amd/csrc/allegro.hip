@@ -527,15 +527,18 @@ __global__ void k_al_geom_bwd(const int *__restrict__ rowc, int n, const float4 
 // Channels (32, 16, 8, 8) of degrees 0..3: tiles 0, 1 are degree 0, tile 2
 // degree 1, tile 3 degree 2 in the lane groups 0, 1 and degree 3 in 2, 3.
 //
-// What bounds it: the chain of dependent layers at two waves per SIMD (vector
-// issue 45 %, LDS 34 %, matrix cores 20 % busy; of a run of 125 edges the sums
-// over atoms and the geometry, whose loads for the next run are issued ahead
-// of phase 3, are a quarter of the time).  Four
-// waves per SIMD need 128 registers and spill (12.0 against 11.5 ms).
-// Measured on 470,596 atoms of fcc aluminium (14.7M edges), split bf16, per
-// evaluation: 64.1 ms with a kernel per step, 11.2 ms with this one; 1,536
-// atoms of water in FP32: 0.84 ms and 0.12 ms (0.20 with one atom to a
-// workgroup and SiLU' formed again in the adjoint).
+// What bounds it: the chain of dependent layers at two waves per SIMD.  Busy,
+// split bf16 at 470,596 atoms: vector issue 44 %, LDS 34 %, matrix cores 25 %,
+// data return of the vector loads 19 %, some instruction issued in 63 % of the
+// cycles; no unit is full.  Of a run of 125 edges the sums over atoms and the
+// geometry, whose loads for the next run are issued ahead of phase 3, are a
+// quarter of the time.  Four waves per SIMD need 128 registers and spill (12.0
+// against 11.5 ms).
+// Measured on 470,596 atoms of fcc aluminium (14.7M edges), split bf16: 64.1 ms
+// per evaluation with a kernel per step, 11.2 ms with this one, which takes
+// 10.8 of them; 1,536 atoms of water in FP32: 0.84 ms and 0.12 ms (the kernel
+// 0.106; 0.20 with one atom to a workgroup and SiLU' formed again in the
+// adjoint).
 // ---------------------------------------------------------------------------
 // (atoms of a run: what LDS holds of env.  With six, a gas of one neighbour per
 // atom filled six rows of 128: 100,000 atoms, split bf16, 1.39 ms, 0.43 so, and

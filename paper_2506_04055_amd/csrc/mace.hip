@@ -520,15 +520,19 @@ __global__ void __launch_bounds__(256) k_mc_conv(const int *__restrict__ rowc, c
 //     V_p,b = sum_c dE/dA_p,c W_p[b][c] gives dE/dR_p = sum_b V_p,b hb_b,
 //     dE/dhb_b += R_p V_p,b and dE/dW_p[b][c] = sum_k dE/dA_p,c R_p hb_b; dE/dR_p
 //     is at once the operand of the transposed output layer.
-// What bounds both: vector and matrix issue together at two waves per SIMD,
-// which the accumulators and one edge's products of a path need (70-80 % of
-// the cycles issue one or the other; SiLU and its derivative are a third of
-// the vector work).  143,748 atoms of fcc aluminium, split bf16: 2.8 + 1.2 ms
-// forward (layers 1 and 0), 4.5 + 2.1 ms adjoint, the evaluation 20.8 -> 14.4
-// ms; 648 atoms of water, FP32, 0.08 + 0.04 and 0.08 + 0.05 ms, 0.70 -> 0.44;
-// an 11k-atom FP32 domain 3.16 -> 2.56 ms.  A forward by runs of atoms with
-// the sums in LDS, as the adjoint has it, took 4.3 + 1.4 ms on the first and
-// 0.065 + 0.026 on the second.
+// What bounds both: vector and matrix work that depend on each other at two
+// waves per SIMD, which the accumulators and one edge's products of a path
+// need.  Busy, split bf16 at 143,748 atoms, layer 1 / layer 0: forward vector
+// issue 29 / 42 %, matrix cores 44 / 33 %, LDS 19 / 21 %; adjoint 43 / 43, 17 /
+// 21 and 23 / 29 %, with the data return of the vector loads at 46 / 41 %.  (In
+// FP32 the adjoint's matrix cores are at 25 / 31 %.)  SiLU and its derivative
+// are a third of the vector work.  143,748 atoms of fcc
+// aluminium, split bf16: 2.75 + 1.18 ms forward (layers 1 and 0), 4.35 + 2.07 ms
+// adjoint, the evaluation 20.8 ms with a kernel per step and 13.4 so; 648 atoms
+// of water, FP32, 0.050 + 0.026 and 0.083 + 0.041 ms, 0.70 and 0.31; an
+// 11k-atom FP32 domain 3.16 and 2.50 ms.  A forward by runs of atoms with the
+// sums in LDS, as the adjoint has it, took 4.3 + 1.4 ms on the first and 0.065
+// + 0.026 on the second.
 // ---------------------------------------------------------------------------
 constexpr int MC_SLOTS = 6;   // atoms of a run (their dE/dA, 5 KB each, fill LDS)
 struct McEdgeArgs {
@@ -1926,7 +1930,7 @@ int mace_evaluate(mlp_model *m, mlp_nbr *g, hipStream_t s, double *energy, float
         k.W = a.chain + (fwd ? a.chF[t] : a.chB[t]);
         k.hb = t ? HB1 : a.hb0tab;
         // the forward hands its atoms out to eight waves: one each as long as
-        // every compute unit has a workgroup, then up to eight each
+        // every compute unit (256 of an MI355X) has a workgroup, then up to eight each
         if (fwd) k.per_wg = nd <= 2048 ? (nd + 255) / 256 : std::max(8, std::min(MC_FWD_ATOMS, nd / 2048));
         const bool split = fwd && k.per_wg <= 4;
         const int nb = nblk(nd, k.per_wg);

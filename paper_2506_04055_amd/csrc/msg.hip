@@ -39,9 +39,10 @@
 // instruction (Basis): per 16 x 16 tile two instructions of 16 cycles for
 // K = 20 split and four for FP32, where one per product took three, and
 // v_mfma_f32_16x16x4_f32 six of 32 cycles.  48k-atom water slab, FP32, F = 128:
-// adjoint 1,460 -> 1,120 us and forward 795 -> 590 us per launch; 24k atoms,
-// split: 476 -> 447 and 268 -> 255 us.  Every sum has a fixed order, so results
-// are bitwise reproducible.
+// adjoint 1,460 -> 1,120 us and forward 795 -> 590 us per launch by this alone
+// (950 and 490 with all that stands below); 24k atoms, split: 476 -> 447 and
+// 268 -> 255 us (357 and 206).  Every sum has a fixed order, so results are
+// bitwise reproducible.
 //
 // The adjoint is organised by source atom j over its in-edges (j <- i), the
 // reverses of the edges (i <- j) that carried j's messages; it gathers the
@@ -713,8 +714,8 @@ inline bool msg_wide(long n, int F) { return n >= (1 << 24) || n * 12 * F > 0xFF
 // four edges in registers, and the sums over the atom's edges need only a
 // sum over the four lane rows at the end.  The basis is evaluated in the
 // layout the MFMA operand takes (lane (e, g): slots of edge e); the source
-// index and direction of the edges 4g + r move to the vector layout by lane
-// shuffles.
+// row and direction of the edges 4g + r are read from the wave's edge records
+// (EdgeRec), written once per chunk.
 // ---------------------------------------------------------------------------
 #ifndef FWD_PIW_WAVES
 #define FWD_PIW_WAVES 16

@@ -15,16 +15,21 @@
 // layers again from s1, v1 and s2 (14 + 16 F floats per atom and layer
 // against 84 F with the intermediates stored and a kernel per product pair).
 //
-// What bounds them, per 16-atom tile of the adjoint at F = 128: 51,000 cycles
-// of matrix cores on one SIMD, and 15,000 each of the compute unit's LDS (the
-// weights) and of its share of HBM, overlapped by two waves per SIMD only.
+// What bounds them: of the 38,500 cycles that a 16-atom tile of the adjoint
+// takes on a compute unit at F = 128 and 1.2M rows, 12,700 are matrix cores (all
+// four SIMDs), 9,000 LDS (the weights), and its bytes are 24,000 at the rate of
+// a copy, overlapped by two waves per SIMD only.
 // The directions are taken one after another, which reads U's and V's blocks
 // three times but holds one direction's operands (32 registers, not 96).
+// Busy at 1.2M rows, forward / adjoint / last layer: the data return of the
+// vector loads 84 / 79 / 70 %, matrix cores 24 / 33 / 36 %, LDS 17 / 23 / 25 %
+// and vector issue 17 / 22 / 23 %, at under two waves per SIMD.
 // Per launch, split bf16, forward / adjoint / last layer: 24,000 atoms of 128
-// features 70 / 121 / 91 us (the chained products they replace: forward 120
-// and the U V product, adjoint 159); 171,500 atoms of 64 features 183 / 257 /
-// 181 (433 and the U V product, 497); 1.2M rows of 128 features 3.4 / 5.4 / 3.4
-// ms (4.3 and the U V product, 6.0).
+// features 66 / 104 / 80 us (the chained products they replace: forward 120
+// and the U V product, adjoint 159); 171,500 atoms of 64 features 178 / 237 /
+// 157 (433 and the U V product, 497); 1.2M rows of 128 features 3.4 / 5.3 / 3.3
+// ms (4.3 and the U V product, 6.0).  FP32, 48,000 atoms of 128 features: 184 /
+// 339 / 268 us.
 //
 // The kernels of one operand form are a translation unit (node_p0.hip ..
 // node_p2.hip: compiled side by side); packing and dispatch are in node.hip.

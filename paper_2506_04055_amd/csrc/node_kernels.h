@@ -109,9 +109,15 @@ using NdRing = EcRing<P, nd_ring(P, NC), nd_pre(P, F, FWD)>;
 constexpr int ND_EU = 2;
 // Rows from which workgroups have seven waves of atoms instead of three (two
 // workgroups per compute unit, whose phases overlap): the weights are then
-// fetched less than half as often, 3 - 6 % of a launch at 1.2M rows, but a
-// launch of 24,000 rows lasts longer (forward 76 against 72 us, adjoint 128
-// against 122), and so do 48,000 (FP32: 379 against 355).
+// fetched less than half as often, 3 - 6 % of a launch at 1.2M rows, but few
+// rows make few workgroups, whose last round is nearly empty.  The node kernels
+// of an evaluation, three against seven waves: split bf16, F = 128: 23,000 rows
+// 455 and 493 us, 49,000 896 and 964, 98,000 1,743 and 1,903, 131,000 2,342 and
+// 2,394, 256,000 4,455 and 4,418, 389,000 6,864 and 6,818; FP32: 49,000 1,341
+// and 1,464, 98,000 2,675 and 2,927, 256,000 6,958 and 7,048.  F = 64, split:
+// 49,000 461 and 511, 98,000 881 and 957, 171,000 1,509 and 1,523; FP32:
+// 256,000 2,949 and 2,905.  Above the line the two stay within 3 % of each
+// other to 400,000 rows.
 constexpr int ND_LARGE = 100000;
 
 template <int P, int F, int NC>
@@ -430,7 +436,6 @@ __global__ void __launch_bounds__(64 * (NC + 1)) __attribute__((amdgpu_waves_per
             g[t] = g2[t];
             rn[t] = z;
         }
-        (void)U1;
         ec_layer<U1, NT, KS>(st, g, [&](auto s) { return y[s]; });
         if (L.ok)
 #pragma unroll
